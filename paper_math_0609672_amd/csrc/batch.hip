@@ -701,7 +701,7 @@ int build_batched_impl(int32_t nmat, const srw_csr* A, int32_t walks_per_row, do
     opt.rank = rank;
     if (opt.solve_order == 2) opt.solve_order = 1;  // the batched solves need the levels
     srw_csr cat{N, NNZ, rowptr, col, val};
-    BatchKeys keys{node_mat, mat_off, mat_seed, level_order};
+    BatchKeys keys{nmat, node_mat, mat_off, mat_seed, level_order};
     srw_factor* F = nullptr;
     const int st = build_factor_impl(&cat, walks_per_row, drop_tol, 0, &opt, &F, s, &keys);
     if (level_order) (void)hipFreeAsync(level_order, s);

@@ -218,12 +218,33 @@ __global__ void k_rank_given(int64_t n, const int32_t* __restrict__ given, int32
 // one XCD share a compact part of the graph and of that XCD's L2.
 constexpr int NSLAB = 8;
 constexpr uint32_t REUSE_STACK = 64;  // walk reuse: stack entries per lane
-// Default waves per CU of the walk kernel.  A walk step is one dependent record load,
-// so the longest walks run at the memory latency the other walks cause: on a 3D grid
-// (128^3, 256 walks per row) 8 waves per CU finish the walks in 165 ms, 12 in 179 ms
-// (an earlier build: 8 in 175 ms, 24 in 205 ms, 4 in 283 ms).
-constexpr int WALK_WAVES_PER_CU = 8;
+// Waves per CU of the walk kernel, where the caller does not set them: those that take
+// walks at once, those that join when the long segment is taken, and those that run
+// handed-over walks.  The lowest ranks' walks wander over the whole graph, and what is in
+// flight competes for the L2s: on the 3D grid 128^3 (256 walks per row) the long segment
+// runs at 6.1e10, 9.3e10 and 5.9e10 steps/s with 4, 8 and 12 waves, the slabs, whose walks
+// stay close, at 6.0e10, 1.08e11 and 1.43e11 (64-byte records).  Whole kernel, near
+// records: 8 + 4 + 8 waves 96 ms, 8 + 0 + 4 106 ms, 8 + 12 + 4 104 ms, 4 + 4 162 ms,
+// 12 + 4 122 ms, 8 + 4 + 12 107 ms.
+//   few walks (less than about 256 per lane): 4 + 0 + 4; the longest walk is what counts,
+//     and every wave's arrival and end are atomics on one address (Laplacian 50^3, 24
+//     walks: 1.14 ms against 1.67; from 2^26 walks on more waves are as fast, and 1.97
+//     against 3.66 ms where walks are short: asymmetric grid 64^3);
+//   walk records past the 256 MB Infinity Cache: 4 + 4 + what fits; random reads from HBM
+//     saturate it and slow the longest walk's own reads (geometric graph 2M: 407 ms,
+//     8 + 0: 447, 8 + 4: 470).
+constexpr int WALK_WAVES_PER_CU = 8, LATE_WAVES_PER_CU = 4, SINGLE_WAVES_PER_CU = 8;
+constexpr int64_t FEW_WALKS = 1 << 25;
+constexpr int64_t MALL_BYTES = (int64_t)256 << 20;
 constexpr int NSEG = NSLAB + 1;
+// Slots for walks handed over from bulk waves to single-walk waves, 32 B each; once they
+// are used up walks stay where they are.
+constexpr int64_t HAND_SLOTS = 1 << 18;
+// The segment queues are 256 bytes apart: atomics on one memory channel queue up, about
+// 11 ns each.
+constexpr int QUEUE_STRIDE = 32;
+constexpr int QUEUE_SUMS = NSEG * QUEUE_STRIDE;  // then degree sum, record count, step sum
+constexpr int QUEUE_WORDS = QUEUE_SUMS + 3;
 
 __global__ void k_flag_long(int64_t n, int64_t long_rank, const int32_t* __restrict__ by_rank,
                             const int32_t* __restrict__ budget, int32_t* flag)
@@ -1490,14 +1511,35 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             bucketing = 0;
         }
         if (2 * n_lines >= (int64_t)UINT32_MAX) FAIL(SRW_E_ARG);  // line indices are 32-bit
+        // near records where the matrix has them (not for the walk kernels that read
+        // lines: walk reuse, refill periods below 8)
+        const int32_t nlist = batch ? batch->nmat : 1;
+        bool near = !reuse && opt.refill_period == 8 && nlist <= NEAR_MATS && n > 0 &&
+                    n_lines == n && n < ((int64_t)1 << 30);
+        int32_t* delta = nullptr;
+        if (near) {
+            delta = ALLOC(tmp, int32_t, nlist * NEAR_DELTAS);
+            if (!delta) FAIL(SRW_E_NOMEM);
+            k_fill_i32v<<<grid_for(nlist * NEAR_DELTAS, BLOCK), BLOCK, 0, s>>>(
+                nlist * NEAR_DELTAS, delta, NO_DELTA);
+            CHECK_HIP(hipMemsetAsync(anyb, 0, sizeof(int32_t), s));
+            k_near_deltas<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, batch ? batch->node_mat : nullptr,
+                                              delta, anyb);
+            CHECK_HIP(hipMemcpyAsync(&pinned[1], anyb, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            CHECK_HIP(hipStreamSynchronize(s));
+            int32_t far = 0;
+            std::memcpy(&far, &pinned[1], sizeof(int32_t));
+            near = far == 0;
+        }
         // walk records, then start records of the same shape
-        uint4* recs = ALLOC(tmp, uint4, 2 * n_lines * 4);
+        const int64_t rec_words = near ? 2 * n * (NEAR_WORDS / 4) : 2 * n_lines * 4;
+        uint4* recs = ALLOC(tmp, uint4, rec_words);
         uint2* ent = opt.keep >= 1 ? ALLOC(keep, uint2, nnz_off) : nullptr;  // export only
-        uint32_t* mthr = ALLOC(xk, uint32_t, nnz_off);
+        uint32_t* mthr = opt.keep >= 1 ? ALLOC(keep, uint32_t, nnz_off) : nullptr;  // likewise
         double* tau = ALLOC(xk, double, n);
         int32_t* budget = ALLOC(xk, int32_t, n);
         int32_t* maxb = ALLOC(tmp, int32_t, 1);
-        if (!recs || (opt.keep >= 1 && !ent) || !mthr || !tau || !budget || !maxb)
+        if (!recs || (opt.keep >= 1 && (!ent || !mthr)) || !tau || !budget || !maxb)
             FAIL(SRW_E_NOMEM);
         F->ent = ent;
         F->mthr = mthr;
@@ -1505,10 +1547,15 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         F->budget = budget;
         mark(2);
         CHECK_HIP(hipMemsetAsync(maxb, 0, sizeof(int32_t), s));
-        k_table<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, F->rank, grounded, walks_per_row,
-                                    opt.walks, plain ? 1 : 0, rline, kbv, bucketing, n_lines,
-                                    (uint32_t*)recs, ent,
-                                    mthr, tau, budget, maxb);
+        if (near)
+            k_table_near<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, F->rank, grounded,
+                                             walks_per_row, opt.walks, plain ? 1 : 0,
+                                             batch ? batch->node_mat : nullptr, delta, recs, ent, mthr,
+                                             tau, budget, maxb);
+        else
+            k_table<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, F->rank, grounded, walks_per_row,
+                                        opt.walks, plain ? 1 : 0, rline, kbv, bucketing, n_lines,
+                                        (uint32_t*)recs, ent, mthr, tau, budget, maxb);
         CHECK_HIP(hipGetLastError());
 
         // record offsets (node order) and the segmented chunk list
@@ -1570,7 +1617,8 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         // a walk's first step reads the row's start record (higher-ranked neighbours
         // only), or for the plain estimator the row's own record
         k_chunks<<<grid_for(norder, BLOCK), BLOCK, 0, s>>>(
-            norder, nlong, order, chunk_off, budget, rline, kbv, plain ? 0 : n_lines, F->rank, rec_off,
+            norder, nlong, order, chunk_off, budget, rline, kbv, plain ? 0 : n_lines, near ? n : 0,
+            F->rank, rec_off,
             seed,
             batch ? batch->node_mat : nullptr, batch ? batch->mat_off : nullptr,
             batch ? batch->mat_seed : nullptr, cdesc);
@@ -1589,9 +1637,9 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             if (!rec_end || !rec_vis || !rec_len) FAIL(SRW_E_NOMEM);
         }
         // segment queues, degree sum, then (walk reuse) record count and step sum
-        unsigned long long* queue = ALLOC(tmp, unsigned long long, NSEG + 3);
+        unsigned long long* queue = ALLOC(tmp, unsigned long long, QUEUE_WORDS);
         if (!queue) FAIL(SRW_E_NOMEM);
-        CHECK_HIP(hipMemsetAsync(queue, 0, (NSEG + 3) * sizeof(unsigned long long), s));
+        CHECK_HIP(hipMemsetAsync(queue, 0, QUEUE_WORDS * sizeof(unsigned long long), s));
         uint64_t* out_key = nullptr;
         uint2* out_vl = nullptr;
         int64_t n_slots = 0;  // walk reuse: record slots taken (records and unused slots)
@@ -1604,7 +1652,10 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         if (n_chunks > 0) {
             WalkArgs wa{};
             wa.recs = recs;
-            wa.lds_lines = (uint32_t)(2 * n_lines);
+            wa.lds_words = (uint32_t)rec_words;
+            wa.delta = delta;
+            wa.n_delta = (uint32_t)(nlist * NEAR_DELTAS);
+            wa.near_n = (uint32_t)(near ? n : 0);
             wa.chunks = cdesc;
             wa.bounds = bounds;
             wa.max_steps = opt.max_steps;
@@ -1616,7 +1667,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             // depend on which wave runs them)
             wa.slab_claim = (uint32_t)std::min<int64_t>(
                 16, std::max<int64_t>(1, 4 * (int64_t)CHUNK_WALKS / std::max<int32_t>(1, max_budget)));
-            wa.deg_sum = queue + NSEG;
+            wa.deg_sum = queue + QUEUE_SUMS;
             wa.err = err;
             int dev = 0, cus = 0;
             CHECK_HIP(hipGetDevice(&dev));
@@ -1629,46 +1680,82 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             const size_t table_bytes = (size_t)(2 * n_lines) * 64;
             const bool lds_table = !reuse && opt.refill_period == 8 && table_bytes <= (size_t)lds_max;
             size_t dyn_lds = 0;
+            const int fmt = near ? REC_NEAR : bucketing ? REC_BUCKETS : REC_LINES;
             if (lds_table) {
-                kern = bucketing ? k_walk_lds<true> : k_walk_lds<false>;
-                dyn_lds = table_bytes;
+                kern = fmt == REC_NEAR ? k_walk_lds<REC_NEAR>
+                                       : fmt == REC_BUCKETS ? k_walk_lds<REC_BUCKETS> : k_walk_lds<REC_LINES>;
+                dyn_lds = (size_t)rec_words * sizeof(uint4);
                 F->walk_lds = 1;
                 CHECK_HIP(hipFuncSetAttribute((const void*)kern,
                                               hipFuncAttributeMaxDynamicSharedMemorySize,
                                               (int)dyn_lds));
             } else if (reuse) {
                 kern = bucketing ? k_walk_reuse<true> : k_walk_reuse<false>;
-            } else if (bucketing) {
-                switch (opt.refill_period) {
-                    case 2: kern = k_walk<2, true>; break;
-                    case 4: kern = k_walk<4, true>; break;
-                    case 8: kern = k_walk<8, true>; break;
-                    default: kern = k_walk<1, true>; break;
-                }
             } else {
                 switch (opt.refill_period) {
-                    case 2: kern = k_walk<2, false>; break;
-                    case 4: kern = k_walk<4, false>; break;
-                    case 8: kern = k_walk<8, false>; break;
-                    default: kern = k_walk<1, false>; break;
+                    case 1: kern = bucketing ? k_walk_refill<1, true> : k_walk_refill<1, false>; break;
+                    case 2: kern = bucketing ? k_walk_refill<2, true> : k_walk_refill<2, false>; break;
+                    case 4: kern = bucketing ? k_walk_refill<4, true> : k_walk_refill<4, false>; break;
+                    default:
+                        kern = fmt == REC_NEAR ? k_walk<REC_NEAR>
+                                               : fmt == REC_BUCKETS ? k_walk<REC_BUCKETS> : k_walk<REC_LINES>;
                 }
             }
             // persistent grid of walk_waves waves per CU (at most what fits)
             int per_cu = 0;
             CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, BLOCK, dyn_lds));
-            const int want = (opt.walk_waves > 0 ? opt.walk_waves : WALK_WAVES_PER_CU) / (BLOCK / 64);
+            const bool hand = !reuse && opt.refill_period == 8 && n_chunks <= (int64_t)UINT32_MAX;
+            int first_w = opt.walk_waves > 0 ? opt.walk_waves : WALK_WAVES_PER_CU;
+            int late_w = 0, single_w = SINGLE_WAVES_PER_CU;
+            if (hand && opt.walk_waves == 0) {
+                if (total_walks < FEW_WALKS) {
+                    first_w = single_w = 4;
+                } else {
+                    late_w = LATE_WAVES_PER_CU;
+                    if (rec_words * 8 > MALL_BYTES) {  // half the records are start records
+                        first_w = 4;
+                        single_w = 64;
+                    }
+                }
+            }
+            const int want = first_w / (BLOCK / 64);
             int64_t blocks = (int64_t)cus * std::max(1, std::min(per_cu, want));
             F->walk_waves = std::max(1, std::min(per_cu, want)) * (BLOCK / 64);
             blocks = std::min<int64_t>(blocks, (n_chunks + BLOCK / 64 - 1) / (BLOCK / 64));
             if (blocks < 1) blocks = 1;
             if (!reuse) {
+                // beside the bulk waves, as far as the chip holds them (k_walk at the
+                // default refill period): more bulk waves for the slabs, then waves for
+                // handed-over walks
+                wa.n_bulk = wa.n_first = (uint32_t)(blocks * (BLOCK / 64));
+                if (hand) {
+                    const int64_t room = std::max<int64_t>(0, (int64_t)cus * std::max(1, per_cu) - blocks);
+                    const int64_t late = std::min(room / 2, (int64_t)cus * late_w / (BLOCK / 64));
+                    const int64_t extra = std::min<int64_t>(
+                        {room, late + (int64_t)cus * single_w / (BLOCK / 64), (total_walks + BLOCK - 1) / BLOCK});
+                    const int64_t cap = std::min<int64_t>(total_walks, HAND_SLOTS);
+                    wa.slots = ALLOC(tmp, unsigned long long, cap * SLOT_WORDS);
+                    wa.hand = ALLOC(tmp, unsigned long long, HAND_WORDS);
+                    if (!wa.slots || !wa.hand) FAIL(SRW_E_NOMEM);
+                    wa.slot_cap = (uint32_t)cap;
+                    wa.n_bulk += (uint32_t)(std::min(late, extra) * (BLOCK / 64));
+                    k_fill_u64<<<std::min(grid_for(cap * SLOT_WORDS, BLOCK), 2048), BLOCK, 0, s>>>(
+                        cap * SLOT_WORDS, wa.slots, SLOT_EMPTY);
+                    k_fill_u64<<<1, BLOCK, 0, s>>>(HAND_WORDS, wa.hand, 0ull);
+                    blocks += extra;
+                    // claims small enough that every bulk wave gets work
+                    wa.slab_claim = (uint32_t)std::max<int64_t>(
+                        1, std::min<int64_t>(wa.slab_claim, n_chunks / (4 * (int64_t)wa.n_bulk)));
+                }
+                // the first waves' first chunks of the long segment are theirs without a claim
+                if (opt.refill_period == 8) k_fill_u64<<<1, 1, 0, s>>>(1, queue, wa.n_first);
                 hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(BLOCK), dyn_lds, s, wa);
                 CHECK_HIP(hipGetLastError());
             } else {
                 wa.stack_depth = REUSE_STACK;
                 wa.stack = ALLOC(tmp, uint4, blocks * BLOCK * REUSE_STACK);
-                wa.nrec = queue + NSEG + 1;
-                wa.steps_sum = queue + NSEG + 2;
+                wa.nrec = queue + QUEUE_SUMS + 1;
+                wa.steps_sum = queue + QUEUE_SUMS + 2;
                 if (!wa.stack) FAIL(SRW_E_NOMEM);
                 // record buffers sized by a first guess; if the walks take more slots,
                 // they run again (same draws, same records) into larger buffers
@@ -1682,10 +1769,10 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
                     wa.out_vl = out_vl;
                     wa.out_cap = (unsigned long long)cap;
                     if (pass > 0)
-                        CHECK_HIP(hipMemsetAsync(queue, 0, (NSEG + 3) * sizeof(unsigned long long), s));
+                        CHECK_HIP(hipMemsetAsync(queue, 0, QUEUE_WORDS * sizeof(unsigned long long), s));
                     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(BLOCK), 0, s, wa);
                     CHECK_HIP(hipGetLastError());
-                    CHECK_HIP(hipMemcpyAsync(&pinned[6], queue + NSEG + 1, 2 * sizeof(int64_t),
+                    CHECK_HIP(hipMemcpyAsync(&pinned[6], queue + QUEUE_SUMS + 1, 2 * sizeof(int64_t),
                                              hipMemcpyDeviceToHost, s));
                     CHECK_HIP(hipMemcpyAsync(&pinned[0], err, sizeof(int), hipMemcpyDeviceToHost, s));
                     CHECK_HIP(hipStreamSynchronize(s));
@@ -1704,7 +1791,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             }
         }
         mark(5);
-        CHECK_HIP(hipMemcpyAsync(&pinned[5], queue + NSEG, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        CHECK_HIP(hipMemcpyAsync(&pinned[5], queue + QUEUE_SUMS, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         CHECK_HIP(hipMemcpyAsync(&pinned[0], err, sizeof(int), hipMemcpyDeviceToHost, s));
         CHECK_HIP(hipStreamSynchronize(s));
         std::memcpy(&herr, &pinned[0], sizeof(int));

@@ -160,6 +160,7 @@ void retain_pool_memory();
 // Walk keys of a batched build: the matrix of every node of the block-diagonal
 // matrix, the first node of every matrix and the matrix's seed.
 struct BatchKeys {
+    int32_t nmat;
     const int32_t* node_mat;
     const int64_t* mat_off;
     const uint64_t* mat_seed;

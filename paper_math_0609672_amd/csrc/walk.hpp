@@ -38,11 +38,60 @@
 // records are bucketed (all main lines below 2^LINE_KB_SHIFT).  The first line and the
 // continuation lines stay: a walk of the plain estimator starts from its row's own
 // record.
+//
+// Near records.  Where every row has at most six neighbours and a matrix's entries lie
+// on at most NEAR_DELTAS diagonals other than the main one (regular grids and stencils
+// in their natural numbering, whatever their size), a record is half a line, 32 bytes:
+// [0] rank | grounded << 31, [1..6] the thresholds (0xFFFFFFFF past the last entry), [7]
+// codes: the neighbour's place in the matrix's list of diagonals, three of four bits
+// for the entry 0, 1, ... (the last neighbour's from there on), the degree in bits 28..30.
+// The chosen entry is the number of thresholds not above the draw; a record's index is
+// its node.  Start records follow from index n on.  Half the bytes per step keep twice
+// the nodes in the L2s (3D grid 128^3: walk kernel 136 -> 100 ms, L2 misses 3.9e9 ->
+// 3.2e9).
 constexpr int REC_WORDS = 16;
 constexpr uint32_t LINE_KB_SHIFT = 27;
 constexpr uint32_t LINE_MASK = (1u << LINE_KB_SHIFT) - 1u;
 constexpr int64_t BUCKET_MAX_DEG = 64;
 constexpr uint32_t DESC_INLINE = 0x40000000u;  // the line's pairs are in words 4..15
+
+enum RecordFormat : int { REC_LINES = 0, REC_BUCKETS = 1, REC_NEAR = 2 };
+constexpr int NEAR_WORDS = 8;
+constexpr uint32_t NEAR_GROUNDED = 0x80000000u;
+constexpr int NEAR_DELTAS = 8;         // diagonals of a matrix, at most
+constexpr int NEAR_MATS = 256;         // matrices of a batch (their lists sit in LDS)
+constexpr int32_t NO_DELTA = INT32_MIN;
+
+// The diagonals j - v of every matrix's entries (delta [matrices][NEAR_DELTAS], NO_DELTA
+// before the launch, in no particular order); *far |= 1 if a row has more than six
+// neighbours or a matrix more than NEAR_DELTAS diagonals.
+__global__ void k_near_deltas(int64_t n, const int64_t* __restrict__ rowptr,
+                              const int32_t* __restrict__ col, const int32_t* __restrict__ node_mat,
+                              int32_t* delta, int32_t* far)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    const int64_t r0 = rowptr[v], r1 = rowptr[v + 1];
+    if (r1 - r0 > 7) {
+        atomicOr(far, 1);
+        return;
+    }
+    int32_t* list = delta + (node_mat ? (int64_t)node_mat[v] * NEAR_DELTAS : 0);
+    for (int64_t p = r0; p < r1; ++p) {
+        const int32_t d = col[p] - (int32_t)v;
+        if (d == 0) continue;
+        int i = 0;
+        for (; i < NEAR_DELTAS; ++i) {
+            int32_t have = __hip_atomic_load(list + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (have == NO_DELTA) have = (int32_t)atomicCAS((int*)list + i, NO_DELTA, d);
+            if (have == d || have == NO_DELTA) break;
+        }
+        if (i == NEAR_DELTAS) {
+            atomicOr(far, 1);
+            return;
+        }
+    }
+}
 
 // Most entries (of nonzero width) that meet one of the 2^kb draw ranges of node v.
 __device__ uint32_t bucket_load(int64_t v, int64_t r0, int64_t r1, const int32_t* __restrict__ col,
@@ -118,6 +167,18 @@ __device__ __forceinline__ uint32_t line_word(const int64_t* __restrict__ rline,
     return (uint32_t)rline[j] | (bucketing ? (uint32_t)kbv[j] << LINE_KB_SHIFT : 0u);
 }
 
+// Walks of row v: walking rows are those with a higher-ranked neighbour (the others are
+// exact), or every row for the plain estimator.
+__device__ __forceinline__ int32_t row_budget(bool walks, int64_t v, int32_t walks_per_row,
+                                              const int32_t* __restrict__ budget_in,
+                                              int32_t* max_budget)
+{
+    if (!walks || walks_per_row == NO_WALKS) return 0;
+    const int32_t b = max(budget_in ? budget_in[v] : walks_per_row, 1);
+    atomicMax(max_budget, b);
+    return b;
+}
+
 __global__ void k_table(int64_t n, const int64_t* __restrict__ rowptr,
                         const int32_t* __restrict__ col, const double* __restrict__ val,
                         const int32_t* __restrict__ rank, const uint8_t* __restrict__ grounded,
@@ -165,7 +226,7 @@ __global__ void k_table(int64_t n, const int64_t* __restrict__ rowptr,
         srec[slot] = mt;
         srec[slot + 1] = line;
         if (ent) ent[start + m] = make_uint2((uint32_t)j, thr);
-        mthr[start + m] = mt;
+        if (mthr) mthr[start + m] = mt;
         last_line = line;
         ++m;
     }
@@ -228,15 +289,79 @@ __global__ void k_table(int64_t n, const int64_t* __restrict__ rowptr,
         }
     }
     tau[v] = motel / a;
-    int32_t b = 0;
-    // walking rows: those with a higher-ranked neighbour (the others are exact), or
-    // every row for the plain estimator
-    if ((motel > 0.0 || plain) && walks_per_row != NO_WALKS) {
-        b = budget_in ? budget_in[v] : walks_per_row;
-        if (b < 1) b = 1;
-        atomicMax(max_budget, b);
+    budget[v] = row_budget(motel > 0.0 || plain, v, walks_per_row, budget_in, max_budget);
+}
+
+// The same for near records.
+__global__ void k_table_near(int64_t n, const int64_t* __restrict__ rowptr,
+                             const int32_t* __restrict__ col, const double* __restrict__ val,
+                             const int32_t* __restrict__ rank, const uint8_t* __restrict__ grounded,
+                             int32_t walks_per_row, const int32_t* __restrict__ budget_in,
+                             int32_t plain, const int32_t* __restrict__ node_mat,
+                             const int32_t* __restrict__ delta, uint4* __restrict__ recs,
+                             uint2* __restrict__ ent, uint32_t* __restrict__ mthr,
+                             double* __restrict__ tau, int32_t* __restrict__ budget,
+                             int32_t* max_budget)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    const int64_t r0 = rowptr[v], r1 = rowptr[v + 1];
+    const int32_t rv = rank[v];
+    double a = 0.0, motel = 0.0;
+    for (int64_t p = r0; p < r1; ++p) {
+        const int32_t j = col[p];
+        if (j == v) a = val[p];
+        else if (rank[j] > rv) motel = motel + (-val[p]);
     }
-    budget[v] = b;
+    const int32_t* list = delta + (node_mat ? (int64_t)node_mat[v] * NEAR_DELTAS : 0);
+    uint32_t t[6], mt[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) t[i] = mt[i] = 0xFFFFFFFFu;
+    const int64_t start = r0 - v;
+    double c = 0.0, cm = 0.0;
+    uint32_t m = 0, codes = 0, last = 0, last_motel = 0;
+    for (int64_t p = r0; p < r1; ++p) {
+        const int32_t j = col[p];
+        if (j == v) continue;
+        const double w = -val[p];
+        c = c + w;
+        uint32_t code = 0;
+        for (uint32_t i = 1; i < (uint32_t)NEAR_DELTAS; ++i)
+            if (list[i] == j - (int32_t)v) code = i;
+        if (rank[j] > rv) {
+            cm = cm + w;
+            last_motel = code;
+        }
+        const uint32_t thr = threshold32(c, a);
+        const uint32_t mthr_m = motel > 0.0 ? threshold32(cm, motel) : 0u;
+#pragma unroll
+        for (uint32_t i = 0; i < 6; ++i)
+            if (i == m) {
+                t[i] = thr;
+                mt[i] = mthr_m;
+            }
+        codes |= code << (4 * m);
+        if (ent) ent[start + m] = make_uint2((uint32_t)j, thr);
+        if (mthr) mthr[start + m] = mthr_m;
+        last = code;
+        ++m;
+    }
+    uint32_t mcodes = codes;
+    for (uint32_t i = m; i < 7; ++i) {  // past every threshold: the last neighbour
+        codes |= last << (4 * i);
+        mcodes |= last_motel << (4 * i);
+    }
+    codes |= m << 28;
+    mcodes |= m << 28;
+    const uint32_t rw = (uint32_t)rv;
+    uint4* rec = recs + (size_t)v * (NEAR_WORDS / 4);
+    uint4* srec = recs + (size_t)(n + v) * (NEAR_WORDS / 4);
+    rec[0] = make_uint4(rw | (grounded[v] ? NEAR_GROUNDED : 0u), t[0], t[1], t[2]);
+    rec[1] = make_uint4(t[3], t[4], t[5], codes);
+    srec[0] = make_uint4(rw, mt[0], mt[1], mt[2]);
+    srec[1] = make_uint4(mt[3], mt[4], mt[5], mcodes);
+    tau[v] = motel / a;
+    budget[v] = row_budget(motel > 0.0 || plain, v, walks_per_row, budget_in, max_budget);
 }
 
 // ----------------------------------------------------------------------- walks
@@ -244,22 +369,27 @@ __global__ void k_table(int64_t n, const int64_t* __restrict__ rowptr,
 struct ChunkDesc {
     uint32_t key;     // Philox key word of the row: its node id (in a batch, its id
                       // within its own matrix)
-    uint32_t walks;   // first walk | count << 16
+    uint32_t walks;   // first walk | count << 13 | matrix (near records of a batch) << 22
     uint32_t sline;   // the row's start record line
     uint32_t rank;    // the row's rank
     uint64_t rec;     // result index of the row's walk 0
     uint64_t seed;    // the seed of the row's matrix
 };
 static_assert(sizeof(ChunkDesc) == 32, "chunk descriptors are 32 bytes");
+// a row has at most 8192 walks, a chunk at most CHUNK_WALKS <= 256 and a batch of near
+// records at most NEAR_MATS matrices
+constexpr int WALKS_FIRST_BITS = 13, WALKS_MAT_SHIFT = 22;
+constexpr uint32_t WALKS_FIRST_MASK = (1u << WALKS_FIRST_BITS) - 1u, WALKS_COUNT_MASK = 0x1FFu;
+static_assert(CHUNK_WALKS <= 256 && NEAR_MATS <= 1024, "chunk descriptor fields");
 
 // chunk descriptors of the rows in schedule order: consecutive walks of a row, SRW_WAVE
 // per chunk for the first nlong rows, CHUNK_WALKS for the others; a walk starts from
 // the first line of the start record (sline_base: the start records) or, with
-// sline_base 0, of the row's own record
+// sline_base 0, of the row's own record; near_n > 0: near records, n of them
 __global__ void k_chunks(int64_t norder, int64_t nlong, const int32_t* __restrict__ order,
                          const int64_t* __restrict__ chunk_off, const int32_t* __restrict__ budget,
                          const int64_t* __restrict__ rline, const uint8_t* __restrict__ kbv,
-                         int64_t sline_base,
+                         int64_t sline_base, int64_t near_n,
                          const int32_t* __restrict__ rank, const int64_t* __restrict__ rec_off,
                          uint64_t seed, const int32_t* __restrict__ node_mat,
                          const int64_t* __restrict__ mat_off, const uint64_t* __restrict__ mat_seed,
@@ -272,34 +402,47 @@ __global__ void k_chunks(int64_t norder, int64_t nlong, const int32_t* __restric
     ChunkDesc d;
     d.key = (uint32_t)v;
     d.seed = seed;
+    uint32_t mat = 0;
     if (node_mat) {
         const int32_t mi = node_mat[v];
+        if (near_n > 0) mat = (uint32_t)mi;
         d.key = (uint32_t)(v - mat_off[mi]);
         d.seed = mat_seed[mi];
     }
-    d.sline = (uint32_t)(sline_base + rline[v] + (kbv[v] ? (1 << kbv[v]) : 0));
+    d.sline = near_n > 0 ? (uint32_t)(sline_base + v)
+                         : (uint32_t)(sline_base + rline[v] + (kbv[v] ? (1 << kbv[v]) : 0));
     d.rank = (uint32_t)rank[v];
     d.rec = (uint64_t)rec_off[v];
     for (int64_t c = chunk_off[j]; c < chunk_off[j + 1]; ++c) {
         const uint32_t cs = j < nlong ? (uint32_t)SRW_WAVE : CHUNK_WALKS;
         const uint32_t w0 = (uint32_t)(c - chunk_off[j]) * cs;
         const uint32_t cnt = min(cs, (uint32_t)b - w0);
-        d.walks = w0 | (cnt << 16);
+        d.walks = w0 | (cnt << WALKS_FIRST_BITS) | (mat << WALKS_MAT_SHIFT);
         cdesc[c] = d;
     }
 }
 
 struct WalkArgs {
     const uint4* recs;         // walk and start records, 4 x 16 bytes per line
-    uint32_t lds_lines;        // lines of recs (k_walk_lds copies them all to LDS)
+    uint32_t lds_words;        // 16-byte words of recs (k_walk_lds copies them all to LDS)
+    const int32_t* delta;      // near records: the matrices' diagonals
+    uint32_t n_delta;          // their number, over all matrices
+    uint32_t near_n;           // near records: nodes (start records follow)
     const ChunkDesc* chunks;
     const int64_t* bounds;     // NSEG + 1 segment starts
     uint64_t max_steps;
     uint32_t* rec_end;
     uint32_t* rec_vis;
     uint32_t* rec_len;
-    unsigned long long* queue;
+    unsigned long long* queue;  // chunks taken of every segment, QUEUE_STRIDE words apart
     uint32_t slab_claim;       // chunks a wave claims at once from a slab queue (>= 1)
+    // long walks handed over to single-walk waves (walk_handed_over)
+    uint32_t n_bulk;               // waves that take walks from the chunk queues
+    uint32_t n_first;              // those of them that start at once; the others once the
+                                   // long segment's rows are taken
+    uint32_t slot_cap;             // slots; 0: no walk is handed over
+    unsigned long long* slots;     // SLOT_WORDS words each, SLOT_EMPTY before the launch
+    unsigned long long* hand;      // HAND_WORDS control words, zero before the launch
     unsigned long long* deg_sum;
     int* err;
     // walk reuse: per-lane stacks of stack_depth entries {rank, node, position,
@@ -372,6 +515,476 @@ __device__ __forceinline__ void emit_walks(const WalkArgs& a, bool em, uint32_t 
     next += cnt;
 }
 
+// ------------------------------------------------------------- handed-over walks
+// The lowest ranks' walks end only at ground and run up to 10^4 times the mean length,
+// one dependent record load per step.  In a bulk wave such a step takes as long as the
+// slowest of 64 random loads and a 64-lane step body: 0.93 us on the 3D grid 128^3 and
+// 1.06 us on the 2M-node geometric graph with every wave busy, 0.56 and 0.84 us on an
+// idle chip.  The load alone takes 0.09 us from L2, 0.27 us from the Infinity Cache and
+// 0.36 us from HBM.  So a lane's walk that has grown old moves to a slot, and a wave that
+// runs nothing else takes it: the walk's state and its records live in scalar registers
+// (one scalar load of the record, compares and selects on the scalar unit), the lanes
+// make the draws, 64 Philox blocks at a time.  A step then takes 0.2 us on the grid and
+// 0.42 us on the graph (idle chip).  Walk kernel with walks handed over, on the same
+// records: graph 780 -> 480 ms; grid 64^3 70 -> 34 ms; the grid 128^3 is bound by the
+// bulk waves.
+//
+// Slots are handed out in order (tail) and taken in order (head, the tickets); a slot's
+// words are each their own ready flag.  A ticket past the tail is a wave waiting for
+// work: it polls its own slot only (thousands of waves polling one address hold up every
+// atomic on that channel by tens of microseconds).  The last bulk wave to finish marks
+// the slots of the tickets past the tail as closed.
+constexpr int SLOT_WORDS = 4;  // {chunk | walk << 32, step << 32 | line word, visits, -}
+constexpr unsigned long long SLOT_EMPTY = ~0ull, SLOT_CLOSED = ~1ull;
+enum : int {
+    HAND_QUEUE = 0,     // tail | head << 32
+    HAND_ARRIVED = 32,  // bulk workgroups that have started
+    HAND_DONE = 64,     // bulk waves that have finished
+    HAND_WORDS = 96
+};
+constexpr uint32_t HAND_MIN_AGE = 64;   // steps before a walk may move
+constexpr uint32_t HAND_GROUPS = 8;     // groups of eight steps between a bulk wave's looks
+constexpr int HAND_WAITING = 256;       // walks kept waiting for a free wave
+constexpr int HAND_PER_LOOK = 2;        // walks a bulk wave hands over per look
+constexpr int HAND_LAST = 4;            // a bulk wave without new work and with this few walks ends
+
+__device__ __forceinline__ unsigned long long hand_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Wave-uniform data of an earlier launch, through the scalar cache.
+template <typename V>
+__device__ __forceinline__ V scalar_load(const void* p)
+{
+    typedef const V __attribute__((address_space(4)))* cptr;
+    return *(cptr)readfirstlane64((uint64_t)p);
+}
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8), aligned(32)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16), aligned(64)));
+
+__device__ __forceinline__ void scalar_line(const uint4* recs, uint32_t line, uint32_t (&w)[16])
+{
+    const u32x16 v = scalar_load<u32x16>(recs + (size_t)line * 4);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = v[i];
+}
+
+__device__ __forceinline__ ChunkDesc scalar_chunk(const ChunkDesc* chunks, uint64_t c)
+{
+    return __builtin_bit_cast(ChunkDesc, scalar_load<u32x8>(chunks + c));
+}
+
+// the record line that a line word and the draw made there select
+template <int FMT>
+__device__ __forceinline__ uint32_t word_line(uint32_t word, uint32_t u)
+{
+    if constexpr (FMT == REC_BUCKETS) {
+        const uint32_t kb = word >> LINE_KB_SHIFT, base = word & LINE_MASK;
+        return kb == 0u ? base : base + (u >> (32u - kb));
+    }
+    return word;
+}
+
+template <int FMT>
+struct SingleRec {
+    uint32_t w[FMT == REC_NEAR ? 8 : 16];
+};
+
+template <int FMT>
+__device__ __forceinline__ SingleRec<FMT> load_single(const uint4* recs, uint32_t line)
+{
+    SingleRec<FMT> r;
+    if constexpr (FMT == REC_NEAR) {
+        const u32x8 v = scalar_load<u32x8>(recs + (size_t)line * (NEAR_WORDS / 4));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r.w[i] = v[i];
+    } else {
+        scalar_line(recs, line, r.w);
+    }
+    return r;
+}
+
+// Runs one walk of row cd to its end, the whole wave on it: t moves are made (a multiple
+// of 8), `word` is the line word of the node reached.  Returns the sum of the degrees of
+// the nodes left.
+template <int FMT>
+__device__ __forceinline__ uint64_t run_single(const WalkArgs& a, const ChunkDesc& cd, uint32_t w,
+                                               uint32_t t, uint32_t word, uint32_t visits)
+{
+    const int lane = __lane_id();
+    const uint64_t limit = a.max_steps;
+    int32_t dl = 0;  // near records: lane i holds the matrix's diagonal i
+    if (FMT == REC_NEAR && lane < NEAR_DELTAS)
+        dl = a.delta[(cd.walks >> WALKS_MAT_SHIFT) * NEAR_DELTAS + lane];
+    uint64_t degsum = 0;
+    uint32_t endv = END_GROUND;
+    uint32_t len = t;
+    bool fin = false;
+    while (!fin) {
+        // lane i makes the eight draws of block len / 8 + i
+        const u64x4 b = philox4x64_10((uint64_t)(len >> 3) + lane, w, cd.key, STREAM_WALK, cd.seed, 0);
+        const uint32_t q[8] = {(uint32_t)b.x0, (uint32_t)(b.x0 >> 32), (uint32_t)b.x1, (uint32_t)(b.x1 >> 32),
+                               (uint32_t)b.x2, (uint32_t)(b.x2 >> 32), (uint32_t)b.x3, (uint32_t)(b.x3 >> 32)};
+        uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)q[0], 0);
+        SingleRec<FMT> r = load_single<FMT>(a.recs, word_line<FMT>(word, u));
+        for (int blk = 0; blk < 64 && !fin; ++blk) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                // the next node, and its record's load, before anything else of this step
+                uint32_t next;
+                bool ground;
+                if constexpr (FMT == REC_NEAR) {
+                    uint32_t sh = 24;  // four times the number of thresholds not above u
+#pragma unroll
+                    for (int i = 6; i >= 1; --i) sh = u < r.w[i] ? 4u * (uint32_t)(i - 1) : sh;
+                    next = word + (uint32_t)__builtin_amdgcn_readlane(dl, (int)((r.w[7] >> sh) & 7u));
+                    ground = sh >= (r.w[7] >> 28) * 4u && (r.w[0] & NEAR_GROUNDED) != 0;
+                } else {
+                    next = ~0u;  // no line word: not found
+                    if (r.w[1] & DESC_INLINE) {
+#pragma unroll
+                        for (int m = 5; m >= 0; --m) next = u < r.w[4 + 2 * m] ? r.w[5 + 2 * m] : next;
+                    } else {
+                        const uint32_t line = word_line<FMT>(word, u);
+                        const uint32_t L = ((r.w[1] & DESC_DEG_MASK) + 7) / 8;
+                        uint32_t l = L > 12 ? 13u : 0u;
+#pragma unroll
+                        for (int i = 11; i >= 0; --i) l = u < r.w[4 + i] ? (uint32_t)(i + 1) : l;
+                        for (; l != 0 && l <= L && next == ~0u; ++l) {
+                            uint32_t f[16];
+                            scalar_line(a.recs, line + l, f);
+#pragma unroll
+                            for (int i = 7; i >= 0; --i) next = u < f[2 * i] ? f[2 * i + 1] : next;
+                        }
+                    }
+                    ground = next == ~0u && (r.w[1] & DESC_GROUNDED) != 0;
+                    next = next == ~0u ? r.w[3] : next;
+                }
+                // (after the last block of a batch: a load that is not used)
+                const uint32_t un = (uint32_t)__builtin_amdgcn_readlane(
+                    (int)q[(j + 1) & 7], j < 7 ? blk : (blk < 63 ? blk + 1 : 63));
+                const SingleRec<FMT> rn = load_single<FMT>(a.recs, word_line<FMT>(next, un));
+                const uint32_t rank = FMT == REC_NEAR ? r.w[0] & ~NEAR_GROUNDED : r.w[0];
+                if (rank <= cd.rank) {
+                    if (rank < cd.rank) {  // home
+                        endv = FMT == REC_NEAR ? word : r.w[2];
+                        fin = true;
+                        break;
+                    }
+                    ++visits;
+                }
+                degsum += FMT == REC_NEAR ? r.w[7] >> 28 : r.w[1] & DESC_DEG_MASK;
+                ++len;
+                if (ground) {
+                    fin = true;
+                    break;
+                }
+                word = next;
+                u = un;
+                r = rn;
+            }
+            if (!fin && len > limit) fin = true;  // past the cap: the build fails
+        }
+    }
+    if (len > limit) {
+        endv = END_LIMIT;
+        if (lane == 0) atomicOr(a.err, ERR_LIMIT);
+    }
+    if (lane == 0) {
+        const uint64_t rec = cd.rec + w;
+        a.rec_end[rec] = endv;
+        a.rec_vis[rec] = visits;
+        a.rec_len[rec] = len;
+    }
+    return degsum;
+}
+
+// A wave that has no other work: takes handed-over walks until none can come any more.
+template <int FMT>
+__device__ __forceinline__ void walk_handed_over(const WalkArgs& a)
+{
+    uint64_t degsum = 0;
+    __builtin_amdgcn_s_setprio(3);  // few instructions per step, all of them on the chain
+    for (;;) {
+        const uint32_t ticket = (uint32_t)(wave_fetch_add(a.hand + HAND_QUEUE, 1ull << 32) >> 32);
+        if (ticket >= a.slot_cap) break;
+        const unsigned long long* slot = a.slots + (size_t)ticket * SLOT_WORDS;
+        uint64_t w0 = readfirstlane64(hand_load(slot)), w1, w2;
+        if (w0 == SLOT_EMPTY && readfirstlane64(hand_load(a.hand + HAND_DONE)) >= a.n_bulk &&
+            ticket >= (uint32_t)readfirstlane64(hand_load(a.hand + HAND_QUEUE)))
+            break;  // the tail is final and this ticket, taken after it was, is past it
+        while (w0 == SLOT_EMPTY) {
+            __builtin_amdgcn_s_sleep(32);
+            w0 = readfirstlane64(hand_load(slot));
+        }
+        if (w0 == SLOT_CLOSED) break;
+        do {  // the other words are there or on their way
+            w1 = readfirstlane64(hand_load(slot + 1));
+            w2 = readfirstlane64(hand_load(slot + 2));
+        } while (w1 == SLOT_EMPTY || w2 == SLOT_EMPTY);
+        const ChunkDesc cd = scalar_chunk(a.chunks, (uint32_t)w0);
+        degsum += run_single<FMT>(a, cd, (uint32_t)(w0 >> 32), (uint32_t)(w1 >> 32), (uint32_t)w1,
+                                  (uint32_t)w2);
+    }
+    if (__lane_id() == 0 && degsum) atomicAdd(a.deg_sum, (unsigned long long)degsum);
+}
+
+// The wave's chunk: the next one of the range it has claimed, else a new claim from the
+// segment it is at (one chunk of the long-walk segment, slab_claim of a slab), else from
+// the next segment that has chunks left: the long-walk segment, the wave's own slab (by
+// the XCD its workgroup runs on), the other slabs in turn.  False once all are taken.
+struct ChunkCursor {
+    uint64_t cur = 0, lim = 0;  // the chunk held and the end of the range claimed
+    int seg = 0;
+    uint32_t first = 0;  // the wave's first chunk of the long segment, not claimed (~0: none)
+    bool begun = false;
+};
+
+__device__ __forceinline__ bool next_chunk(const WalkArgs& a, int home, ChunkCursor& k)
+{
+    if (k.cur + 1 < k.lim) {
+        ++k.cur;
+        return true;
+    }
+    const int lane = __lane_id();
+    for (;;) {
+        const uint64_t b0 = scalar_load<uint64_t>(a.bounds + k.seg);
+        const uint64_t size = scalar_load<uint64_t>(a.bounds + k.seg + 1) - b0;
+        const uint64_t n = k.seg == 0 ? 1ull : (uint64_t)a.slab_claim;
+        const uint64_t c = !k.begun ? (uint64_t)k.first : size ? wave_fetch_add(&a.queue[k.seg * QUEUE_STRIDE], n) : 0ull;
+        k.begun = true;
+        if (c < size) {
+            k.cur = b0 + c;
+            k.lim = b0 + (c + n < size ? c + n : size);
+            return true;
+        }
+        // one look at all the queues rather than one contended atomic at each
+        const bool left = lane < NSEG && hand_load(&a.queue[lane * QUEUE_STRIDE]) <
+                                             (unsigned long long)(a.bounds[lane + 1] - a.bounds[lane]);
+        const uint32_t m = (uint32_t)ballot(left);
+        if (m == 0) return false;
+        if (m & 1u) {
+            k.seg = 0;
+        } else {
+            const uint32_t s = m >> 1, h = (uint32_t)home;
+            k.seg = 1 + (int)((h + (uint32_t)__ffs((int)((s >> h) | (s << (NSLAB - h)))) - 1u) % NSLAB);
+        }
+    }
+}
+
+// Bulk walk kernel body.  Every wave owns up to 64 walks at a time, one per lane, and
+// runs in groups of eight steps, one Philox block per lane and group.  Before a group
+// the idle lanes take the next walks of the current chunk.  A step loads the record of
+// the node the lane is at (first the row's start record), tests it for home, and
+// selects the next node from it: one dependent load per step.  Every lane runs every
+// step; an idle lane sits at record 0 and keeps nothing.  A finished walk's results are
+// stored just after the next record load is issued: stored at once, they would have to
+// complete before that load could reuse their registers.
+// recs: the records (a.recs, or the workgroup's copy of them in LDS); dict: the
+// diagonals of near records, in LDS.
+template <int FMT>
+__device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, const int32_t* dict,
+                                          uint32_t first)
+{
+    const int lane = __lane_id();
+    const uint64_t lt = lanemask_lt();
+    const int home_slab = (int)(blockIdx.x % NSLAB);
+    const uint32_t limit = (uint32_t)(a.max_steps < 0xFFFFFF00ull ? a.max_steps : 0xFFFFFF00ull);
+    // wave-uniform chunk state
+    ChunkCursor cur;
+    cur.first = first;
+    ChunkDesc cd{};
+    uint32_t c_next = 0, c_end = 0;
+    bool done = false;
+    // per-lane walk state
+    bool active = false, pend = false;
+    uint32_t key = 0, w = 0, t = 0, visits = 0, rank_k = 0, cidx = 0, word = 0, dbase = 0;
+    uint32_t endv = 0, len = 0;  // of the finished walk whose results wait
+    uint64_t rec = 0, seedw = 0, degsum = 0;
+
+    for (uint32_t g = 0;; ++g) {
+        if (pend) {
+            a.rec_end[rec] = endv;
+            a.rec_vis[rec] = visits;
+            a.rec_len[rec] = len;
+            pend = false;
+        }
+        // Old walks move to single-walk waves.  While walks are still to be started: those
+        // that have been running for at least half of this wave's time, if few are
+        // waiting for a wave (the longest walks start first, so they are the oldest at any
+        // time).  Afterwards: any walk, if a wave is idle; and the last few walks of a
+        // wave all at once.
+        if (a.slot_cap != 0 && g != 0 && g % (done ? 2u : HAND_GROUPS) == 0) {
+            const uint64_t act = ballot(active);
+            const uint64_t cand = done ? act
+                                       : ballot(active && t >= HAND_MIN_AGE && t >= 4 * g && t < 0x40000000u);
+            if (cand != 0) {
+                int room = HAND_LAST;
+                if (!done || __popcll(act) > HAND_LAST) {
+                    const uint64_t qs = readfirstlane64(hand_load(a.hand + HAND_QUEUE));
+                    const int waiting = (int)((uint32_t)qs - (uint32_t)(qs >> 32));
+                    if (!done) room = waiting < HAND_WAITING ? HAND_PER_LOOK : 0;
+                    else if (waiting >= 0) room = 0;
+                    if ((uint32_t)qs >= a.slot_cap) room = 0;
+                }
+                const int place = (int)__popcll(cand & lt);
+                const bool go = ((cand >> lane) & 1ull) && place < room;
+                const uint32_t cnt = (uint32_t)__popcll(ballot(go));
+                if (cnt != 0) {
+                    const uint32_t at = (uint32_t)wave_fetch_add(a.hand + HAND_QUEUE, cnt) + (uint32_t)place;
+                    if (go && at < a.slot_cap) {
+                        unsigned long long* sl = a.slots + (size_t)at * SLOT_WORDS;
+                        const unsigned long long words[3] = {
+                            (unsigned long long)cidx | (unsigned long long)w << 32,
+                            (unsigned long long)t << 32 | word, (unsigned long long)visits};
+                        for (int i = 0; i < 3; ++i)
+                            __hip_atomic_store(sl + i, words[i], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                        active = false;
+                        word = 0;
+                    }
+                }
+            }
+        }
+        if (!done) {
+            uint64_t idle = ballot(!active);
+            while (idle != 0) {
+                if (c_next >= c_end) {
+                    if (!next_chunk(a, home_slab, cur)) {
+                        done = true;
+                        break;
+                    }
+                    cd = scalar_chunk(a.chunks, cur.cur);
+                    c_next = cd.walks & WALKS_FIRST_MASK;
+                    c_end = c_next + ((cd.walks >> WALKS_FIRST_BITS) & WALKS_COUNT_MASK);
+                }
+                const uint32_t avail = c_end - c_next;
+                const uint32_t pos = (uint32_t)__popcll(idle & lt);
+                const bool take = ((idle >> lane) & 1ull) && pos < avail;
+                if (take) {
+                    key = cd.key;
+                    w = c_next + pos;
+                    t = 0;
+                    visits = 0;
+                    active = true;
+                    rank_k = cd.rank;
+                    seedw = cd.seed;
+                    rec = cd.rec + w;
+                    word = cd.sline;
+                    cidx = (uint32_t)cur.cur;
+                    if (FMT == REC_NEAR) dbase = (cd.walks >> WALKS_MAT_SHIFT) * NEAR_DELTAS;
+                }
+                const uint64_t taken = ballot(take);
+                c_next += (uint32_t)__popcll(taken);
+                idle &= ~taken;
+            }
+        }
+        if (ballot(active) == 0) {
+            if (done) break;
+            continue;
+        }
+        // draw t + j is the word j of the Philox block t / 8
+        const u64x4 b = philox4x64_10((uint64_t)(t >> 3), w, key, STREAM_WALK, seedw, 0);
+        const uint32_t q[8] = {(uint32_t)b.x0, (uint32_t)(b.x0 >> 32), (uint32_t)b.x1, (uint32_t)(b.x1 >> 32),
+                               (uint32_t)b.x2, (uint32_t)(b.x2 >> 32), (uint32_t)b.x3, (uint32_t)(b.x3 >> 32)};
+        uint32_t dacc = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t u = q[j];
+            uint32_t rank, id, deg, next;
+            bool ground;
+            if constexpr (FMT == REC_NEAR) {
+                const uint4* lp = recs + (size_t)word * (NEAR_WORDS / 4);
+                const uint4 x0 = lp[0], x1 = lp[1];
+                if (pend) {
+                    a.rec_end[rec] = endv;
+                    a.rec_vis[rec] = visits;
+                    a.rec_len[rec] = len;
+                    pend = false;
+                }
+                // only a group's first step can be at a start record
+                id = j == 0 && word >= a.near_n ? word - a.near_n : word;
+                rank = x0.x & ~NEAR_GROUNDED;
+                deg = (x1.w >> 28) & 7u;
+                uint32_t sh = 24;  // four times the number of thresholds not above u
+                sh = u < x1.z ? 20u : sh;
+                sh = u < x1.y ? 16u : sh;
+                sh = u < x1.x ? 12u : sh;
+                sh = u < x0.w ? 8u : sh;
+                sh = u < x0.z ? 4u : sh;
+                sh = u < x0.y ? 0u : sh;
+                next = id + (uint32_t)dict[dbase + ((x1.w >> sh) & 7u)];
+                ground = sh >= 4u * deg && (x0.x & NEAR_GROUNDED) != 0;
+            } else {
+                const uint32_t line = word_line<FMT>(word, u);
+                const uint4* lp = recs + (size_t)line * 4;
+                const uint4 r0 = lp[0], r1 = lp[1], r2 = lp[2], r3 = lp[3];
+                if (pend) {
+                    a.rec_end[rec] = endv;
+                    a.rec_vis[rec] = visits;
+                    a.rec_len[rec] = len;
+                    pend = false;
+                }
+                const uint32_t e[16] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w,
+                                        r2.x, r2.y, r2.z, r2.w, r3.x, r3.y, r3.z, r3.w};
+                rank = e[0];
+                id = e[2];
+                deg = e[1] & DESC_DEG_MASK;
+                next = ~0u;  // no line word: not found
+                if (!active || (e[1] & DESC_INLINE) != 0u) {
+                    // the first entry m with u < threshold_m, scanned from the top with
+                    // selects; unused entries are zero words, and no u is below zero
+#pragma unroll
+                    for (int m = 5; m >= 0; --m) next = u < e[4 + 2 * m] ? e[5 + 2 * m] : next;
+                } else {
+                    // the first of the (up to twelve) summarised lines whose last threshold
+                    // exceeds u holds the entry; beyond twelve lines, scan on from line 13
+                    const uint32_t L = (deg + 7) / 8;
+                    uint32_t l = L > 12 ? 13u : 0u;
+#pragma unroll
+                    for (int i = 11; i >= 0; --i)  // summaries past the last line are zero
+                        l = u < e[4 + i] ? (uint32_t)(i + 1) : l;
+                    for (; l != 0 && l <= L && next == ~0u; ++l) {
+                        const uint4* fp = recs + (size_t)(line + l) * 4;
+                        const uint4 f0 = fp[0], f1 = fp[1], f2 = fp[2], f3 = fp[3];
+                        const uint32_t f[16] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w,
+                                                f2.x, f2.y, f2.z, f2.w, f3.x, f3.y, f3.z, f3.w};
+#pragma unroll
+                        for (int i = 7; i >= 0; --i) next = u < f[2 * i] ? f[2 * i + 1] : next;
+                    }
+                }
+                ground = next == ~0u && (e[1] & DESC_GROUNDED) != 0;
+                next = next == ~0u ? e[3] : next;  // (rounding) past every threshold
+            }
+            const bool home = active && rank < rank_k;
+            const bool move = active && !home;
+            visits += rank == rank_k ? 1u : 0u;
+            dacc += move ? deg : 0u;
+            if (home || (move && ground)) {
+                endv = home ? id : END_GROUND;
+                len = t + (uint32_t)j + (home ? 0u : 1u);
+                if (len > limit) atomicOr(a.err, ERR_LIMIT);
+                pend = true;
+                active = false;
+            }
+            word = active ? next : 0u;
+        }
+        degsum += dacc;
+        t += 8;
+        if (active && t > limit) {  // past the cap: the build fails
+            atomicOr(a.err, ERR_LIMIT);
+            endv = END_LIMIT;
+            len = t;
+            pend = true;
+            active = false;
+            word = 0;
+        }
+    }
+    degsum = wave_sum(degsum);
+    if (lane == 0 && degsum) atomicAdd(a.deg_sum, (unsigned long long)degsum);
+}
+
 // Persistent walk kernel.  Every wave owns up to 64 walks at a time, one per lane.
 // Every R steps the idle lanes of a wave take the next walks of the current chunk;
 // an exhausted chunk is replaced by the next one from the segment queues: the
@@ -393,10 +1006,10 @@ __device__ __forceinline__ void emit_walks(const WalkArgs& a, bool em, uint32_t 
 #ifndef SRW_WALK_WAVES
 #define SRW_WALK_WAVES 4  // waves per SIMD the register budget is cut for (the grid runs 2)
 #endif
-// recs: the records (a.recs, or the workgroup's copy of them in LDS)
 template <int R, bool REUSE, bool BUCKETS>
-__device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
+__device__ __forceinline__ void walk_body(const WalkArgs& a)
 {
+    const uint4* const recs = a.recs;
     const int lane = __lane_id();
     const uint64_t lt = lanemask_lt();
     // wave-uniform chunk state
@@ -419,13 +1032,6 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
         REUSE ? a.stack + ((size_t)blockIdx.x * BLOCK + threadIdx.x) * a.stack_depth : nullptr;
     uint64_t steps_acc = 0;
     uint64_t blk_next = 0, blk_end = 0;  // the wave's block of record slots
-    // LOCK: a finished walk's result waits one iteration and is stored just after the
-    // next record load is issued.  Stored at once, the wave had to wait for the stores
-    // to complete before that load could reuse their registers: a store round trip
-    // in front of nearly every step.
-    bool pend = false;
-    uint64_t pend_rec = 0;
-    uint32_t pend_end = 0, pend_vis = 0, pend_len = 0;
 
     for (uint32_t iter = 0;; ++iter) {
         if ((iter % R) == 0 && !done) {
@@ -442,8 +1048,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
                         const unsigned long long size =
                             (unsigned long long)(a.bounds[sq + 1] - a.bounds[sq]);
                         const unsigned long long k = sq == 0 ? 1ull : (unsigned long long)a.slab_claim;
-                        const unsigned long long c =
-                            lane0_u64(atomicAdd(&a.queue[sq], lane == 0 ? k : 0ull));
+                        const unsigned long long c = wave_fetch_add(&a.queue[sq * QUEUE_STRIDE], k);
                         if (c < size) {
                             got = true;
                             cidx = (unsigned long long)a.bounds[sq] + c;
@@ -457,8 +1062,8 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
                     }
                     if (done) break;
                     cd = a.chunks[cidx];
-                    c_next = cd.walks & 0xFFFFu;
-                    c_end = c_next + (cd.walks >> 16);
+                    c_next = cd.walks & WALKS_FIRST_MASK;
+                    c_end = c_next + ((cd.walks >> WALKS_FIRST_BITS) & WALKS_COUNT_MASK);
                 }
                 const uint32_t avail = c_end - c_next;
                 const uint32_t pos = (uint32_t)__popcll(idle & lt);
@@ -495,16 +1100,11 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
             if (done) break;
             continue;
         }
-        // LOCK (refill period 8, no reuse): every lane runs the step; an idle lane takes
-        // no entry and loads line 0 (any record line will do), and keeps no result.
-        // Active lanes started their walks at multiples of 8 iterations, so t and the
-        // iteration count agree mod 8 and the random block refresh is wave-uniform.
-        constexpr bool LOCK = !REUSE && R == 8;
-        if (LOCK || active) {  // structured: the lanes rejoin before the next refill's ballots
+        if (active) {  // structured: the lanes rejoin before the next refill's ballots
         // draws: step t's is the word t mod 8 of the Philox block t div 8.  With bucket
         // lines a walk needs its next draw during a step, so the next block is made at
         // the block's last step and the first block when the walk starts.
-        const uint32_t phase = LOCK ? (iter & 7u) : (uint32_t)(t & 7);
+        const uint32_t phase = (uint32_t)(t & 7);
         if (phase == 0 && (!BUCKETS || t == 0)) {
             const u64x4 b = philox4x64_10(t >> 3, w, key, STREAM_WALK, seedw, 0);
             q0 = (uint32_t)b.x0; q1 = (uint32_t)(b.x0 >> 32);
@@ -524,10 +1124,9 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
             }
         }
 
-        const uint32_t deg = (!LOCK || active) ? (r0.y & DESC_DEG_MASK) : 0u;
+        const uint32_t deg = r0.y & DESC_DEG_MASK;
         degsum += deg;
-        // an idle lane takes the in-line path: it loads nothing more
-        const bool inl = (LOCK && !active) || (r0.y & DESC_INLINE) != 0u;
+        const bool inl = (r0.y & DESC_INLINE) != 0u;
         // The next node is the first entry m with u < threshold_m; the words of the
         // line held (a narrow record, a bucket line, or a wide record's first line)
         // are in registers.
@@ -584,19 +1183,12 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
             const uint32_t base = next_line & LINE_MASK;
             next_line = kb == 0u ? base : base + (q0 >> (32u - kb));
         }
-        if (LOCK && !active) next_line = 0;
         const uint4* lp = recs + (size_t)next_line * 4;
         r0 = lp[0];
         r1 = lp[1];
         r2 = lp[2];
         r3 = lp[3];
         cline = next_line;
-        if (LOCK && pend) {  // the previous iteration's finished walk, behind this load
-            a.rec_end[pend_rec] = pend_end;
-            a.rec_vis[pend_rec] = pend_vis;
-            a.rec_len[pend_rec] = pend_len;
-            pend = false;
-        }
         // home: a node ranked below the row (the first step only reaches higher ranks)
         bool fin = to_ground || r0.x < rank_k;
         uint32_t endv = to_ground ? END_GROUND : r0.z;
@@ -639,8 +1231,7 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
             }
         }
         ++t;
-        if (LOCK && !active) fin = false;  // an idle lane keeps nothing
-        if (!fin && active && t >= a.max_steps) {
+        if (!fin && t >= a.max_steps) {
             fin = true;
             endv = END_LIMIT;
             atomicOr(a.err, ERR_LIMIT);
@@ -648,12 +1239,6 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
         if (fin) {
             if constexpr (REUSE) {
                 steps_acc += t;
-            } else if constexpr (LOCK) {
-                pend = true;
-                pend_rec = rec;
-                pend_end = endv;
-                pend_vis = visits;
-                pend_len = (uint32_t)t;
             } else {
                 a.rec_end[rec] = endv;
                 a.rec_vis[rec] = visits;
@@ -671,11 +1256,6 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
         for (uint64_t q = blk_next + lane; q < blk_end; q += 64)
             if (q < a.out_cap) a.out_key[q] = ~0ull;
     }
-    if (pend) {  // LOCK: the last finished walk of the lane
-        a.rec_end[pend_rec] = pend_end;
-        a.rec_vis[pend_rec] = pend_vis;
-        a.rec_len[pend_rec] = pend_len;
-    }
     degsum = wave_sum(degsum);
     if (lane == 0 && degsum) atomicAdd(a.deg_sum, (unsigned long long)degsum);
     if constexpr (REUSE) {
@@ -684,29 +1264,89 @@ __device__ __forceinline__ void walk_body(const WalkArgs& a, const uint4* recs)
     }
 }
 
-// BUCKETS: some records have bucket lines (line words carry bucket exponents)
+// refill periods other than 8
 template <int R, bool BUCKETS>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRW_WALK_WAVES))) void k_walk(WalkArgs a)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRW_WALK_WAVES))) void k_walk_refill(WalkArgs a)
 {
-    walk_body<R, false, BUCKETS>(a, a.recs);
-}
-
-// The same walks with the records staged in LDS: for a table of at most the LDS a
-// workgroup can hold (a.lds_lines lines of 64 bytes, walk and start records), every
-// workgroup first copies it, and each step then reads LDS instead of the caches.
-template <bool BUCKETS>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRW_WALK_WAVES))) void k_walk_lds(WalkArgs a)
-{
-    extern __shared__ uint4 table[];
-    const int64_t words = (int64_t)a.lds_lines * 4;
-    for (int64_t i = threadIdx.x; i < words; i += BLOCK) table[i] = a.recs[i];
-    __syncthreads();
-    walk_body<8, false, BUCKETS>(a, table);
+    walk_body<R, false, BUCKETS>(a);
 }
 
 // walk reuse keeps the stack top in registers as well: a larger register budget
 template <bool BUCKETS>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_walk_reuse(WalkArgs a)
 {
-    walk_body<8, true, BUCKETS>(a, a.recs);
+    walk_body<8, true, BUCKETS>(a);
+}
+
+// Each wave's part: a bulk wave, then (a.slot_cap) a single-walk wave.  Bulk waves wait
+// for no one while they have work.  A later workgroup waits (for the long segment to be
+// taken, for handed-over walks) only if every bulk workgroup has started, so no wait can
+// keep the chip from a wave that it depends on, in whatever order the workgroups are
+// dispatched; else a late bulk wave starts at once and a single-walk wave ends (the bulk
+// waves take over the walks handed over when they finish).
+template <int FMT>
+__device__ __forceinline__ void walk_wave(const WalkArgs& a, const uint4* recs, const int32_t* dict)
+{
+    __shared__ int all_here;
+    const bool hand = a.slot_cap != 0;
+    const uint32_t wave = blockIdx.x * (BLOCK / 64) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool bulk = wave < a.n_bulk;
+    bool here = true;
+    if (hand) {
+        if (bulk && threadIdx.x == 0) atomicAdd(a.hand + HAND_ARRIVED, 1ull);
+        if (wave >= a.n_first) {
+            if (threadIdx.x == 0) {
+                int ok = 0;
+                for (int i = 0; i < 64 && !ok; ++i) {
+                    ok = hand_load(a.hand + HAND_ARRIVED) >= a.n_bulk / (BLOCK / 64);
+                    if (!ok) __builtin_amdgcn_s_sleep(64);
+                }
+                all_here = ok;
+            }
+            __syncthreads();  // n_first and n_bulk are whole workgroups
+            here = all_here != 0;
+        }
+    }
+    if (bulk) {
+        if (hand && wave >= a.n_first && here) {
+            const unsigned long long size = (unsigned long long)(a.bounds[1] - a.bounds[0]);
+            while (readfirstlane64(hand_load(a.queue)) < size) __builtin_amdgcn_s_sleep(127);
+        }
+        walk_bulk<FMT>(a, recs, dict, wave < a.n_first ? wave : ~0u);
+        if (hand && wave_fetch_add(a.hand + HAND_DONE, 1ull) == a.n_bulk - 1u) {
+            // the last one: the tickets past the tail, and their slots
+            const uint64_t qs = wave_fetch_add(a.hand + HAND_QUEUE, 0ull);
+            const uint32_t head = min((uint32_t)(qs >> 32), a.slot_cap);
+            for (uint32_t i = (uint32_t)qs + __lane_id(); i < head; i += 64)
+                __hip_atomic_store(a.slots + (size_t)i * SLOT_WORDS, SLOT_CLOSED, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (hand && here) walk_handed_over<FMT>(a);
+}
+
+template <int FMT>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRW_WALK_WAVES))) void k_walk(WalkArgs a)
+{
+    __shared__ int32_t dict[FMT == REC_NEAR ? NEAR_MATS * NEAR_DELTAS : 1];
+    if (FMT == REC_NEAR) {
+        for (uint32_t i = threadIdx.x; i < a.n_delta; i += BLOCK) dict[i] = a.delta[i];
+        __syncthreads();
+    }
+    walk_wave<FMT>(a, a.recs, dict);
+}
+
+// The same walks with the records staged in LDS: for a table of at most the LDS a
+// workgroup can hold, every workgroup first copies it, and each step of a bulk wave then
+// reads LDS instead of the caches.
+template <int FMT>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(SRW_WALK_WAVES))) void k_walk_lds(WalkArgs a)
+{
+    extern __shared__ uint4 table[];
+    __shared__ int32_t dict[FMT == REC_NEAR ? NEAR_MATS * NEAR_DELTAS : 1];
+    for (uint32_t i = threadIdx.x; i < a.lds_words; i += BLOCK) table[i] = a.recs[i];
+    if (FMT == REC_NEAR)
+        for (uint32_t i = threadIdx.x; i < a.n_delta; i += BLOCK) dict[i] = a.delta[i];
+    __syncthreads();
+    walk_wave<FMT>(a, table, dict);
 }
