@@ -648,10 +648,10 @@ int build_batched_impl(int32_t nmat, const srw_csr* A, int32_t walks_per_row, do
         char* ws = nullptr;
         const size_t rt = radix_tmp_bytes(N);
         const size_t bytes = (size_t)N * (2 * sizeof(uint64_t) + 4 * sizeof(uint32_t)) + rt + 256;
-        if ((e = hipMallocAsync((void**)&ws, bytes, s)) != hipSuccess)
+        if ((e = dev_alloc((void**)&ws, bytes)) != hipSuccess)
             return fail(hip_fail(e, "batched ordering"));
-        if ((e = hipMallocAsync((void**)&level_order, (size_t)N * sizeof(int32_t), s)) != hipSuccess) {
-            (void)hipFreeAsync(ws, s);
+        if ((e = dev_alloc((void**)&level_order, (size_t)N * sizeof(int32_t))) != hipSuccess) {
+            dev_release(ws);
             return fail(hip_fail(e, "batched ordering"));
         }
         uint64_t* k64 = (uint64_t*)ws;
@@ -690,9 +690,11 @@ int build_batched_impl(int32_t nmat, const srw_csr* A, int32_t walks_per_row, do
             k_copy_u32_i32<<<g, BLOCK, 0, s>>>(N, vo, level_order);
             e = hipGetLastError();
         }
-        (void)hipFreeAsync(ws, s);
+        const hipError_t es = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = es;
+        dev_release(ws);
         if (e != hipSuccess) {
-            (void)hipFreeAsync(level_order, s);
+            dev_release(level_order);
             return fail(hip_fail(e, "batched ordering"));
         }
     }
@@ -704,7 +706,8 @@ int build_batched_impl(int32_t nmat, const srw_csr* A, int32_t walks_per_row, do
     BatchKeys keys{nmat, node_mat, mat_off, mat_seed, level_order};
     srw_factor* F = nullptr;
     const int st = build_factor_impl(&cat, walks_per_row, drop_tol, 0, &opt, &F, s, &keys);
-    if (level_order) (void)hipFreeAsync(level_order, s);
+    (void)hipStreamSynchronize(s);
+    dev_release(level_order);
     if (st != SRW_OK) return fail(st);
     F->nmat = nmat;
     F->mat_off_host = off;
@@ -912,7 +915,7 @@ int apply_batched_impl(srw_factor* F, int32_t nrhs, const double* R, double* Z, 
     const size_t vb = F->precision == SRW_FP32 ? sizeof(float) : sizeof(double);
     const size_t o_flag = ((2 * nv * vb) + 255) & ~(size_t)255;
     char* ws = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&ws, o_flag + 128, s));
+    SRW_HIP(dev_alloc((void**)&ws, o_flag + 128));
     W.r = const_cast<double*>(R);
     W.z = Z;
     W.work = ws;
@@ -933,9 +936,9 @@ int apply_batched_impl(srw_factor* F, int32_t nrhs, const double* R, double* Z, 
     if (e == hipSuccess) e = apply_b(F, W, sc, s);
     int herr[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(herr, W.active, 2 * sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    const hipError_t fe = hipFreeAsync(ws, s);
-    if (e == hipSuccess) e = fe;
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ws);
     if (e != hipSuccess) {
         set_last_error(hipGetErrorString(e));
         return SRW_E_HIP;
@@ -978,8 +981,9 @@ int pcg_batched_impl(srw_factor* F, int32_t nrhs, const double* B, double tol, i
     const size_t o_flag = take(128);
     const size_t o_tm = take(std::max<int64_t>(W.ntile, 1) * 4), o_tr = take((W.ntile + 1) * 8);
     const size_t o_mt = take((F->nmat + 1) * 8);
+    std::vector<Sys> host_sys((size_t)std::max<int64_t>(W.nsys, 1));
     char* ws = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&ws, bytes, s));
+    SRW_HIP(dev_alloc((void**)&ws, bytes));
     W.r = (double*)(ws + o_r);
     W.z = (double*)(ws + o_z);
     W.p = (double*)(ws + o_p);
@@ -995,11 +999,13 @@ int pcg_batched_impl(srw_factor* F, int32_t nrhs, const double* B, double tol, i
     int64_t* d_trow = (int64_t*)(ws + o_tr);
     W.mat_tile = (int64_t*)(ws + o_mt);
     W.tiles = Tiles{d_tmat, d_trow};
-    Sys* host_sys = nullptr;
-    int* host_flag = nullptr;
-    hipError_t e = hipHostMalloc((void**)&host_sys, std::max<int64_t>(W.nsys, 1) * sizeof(Sys), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&host_flag, 16 * sizeof(int), hipHostMallocDefault);
-    if (host_flag) std::memset(host_flag, 0, 16 * sizeof(int));
+    int* host_flag = host_scratch() ? (int*)(host_scratch() + 20) : nullptr;
+    if (!host_flag) {
+        dev_release(ws);
+        return hip_fail(hipErrorOutOfMemory, "hipHostMalloc");
+    }
+    hipError_t e = hipSuccess;
+    std::memset(host_flag, 0, 16 * sizeof(int));
     Sched tuning{};  // schedule being timed when a solve failed (per_cu 0: not while tuning)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1147,7 +1153,7 @@ int pcg_batched_impl(srw_factor* F, int32_t nrhs, const double* B, double tol, i
             e = hipGetLastError();
         }
     }
-    CK(hipMemcpyAsync(host_sys, W.sys, W.nsys * sizeof(Sys), hipMemcpyDeviceToHost, s));
+    CK(hipMemcpyAsync(host_sys.data(), W.sys, W.nsys * sizeof(Sys), hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
     if (e == hipSuccess) {
         if (host_flag[1] != 0) {
@@ -1176,10 +1182,8 @@ int pcg_batched_impl(srw_factor* F, int32_t nrhs, const double* B, double tol, i
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     if (cs) (void)hipStreamDestroy(cs);
-    (void)hipFreeAsync(ws, s);
     (void)hipStreamSynchronize(s);
-    if (host_sys) (void)hipHostFree(host_sys);
-    if (host_flag) (void)hipHostFree(host_flag);
+    dev_release(ws);
     if (e != hipSuccess) return hip_fail(e, where);
     return status;
 }

@@ -13,6 +13,7 @@
 // hidden activations are rounded to bfloat16 (nearest, ties to even) before each
 // product; in the backward pass the pre-activation gradients dZ2 and dZ1 are rounded
 // the same way.  Every sum is fp32; reductions run in a fixed order.
+#include <atomic>
 #include <cmath>
 
 #include "factor.hpp"
@@ -471,13 +472,14 @@ int features_impl(const srw_csr* A, const int32_t* rank, float* feat, hipStream_
     const int64_t n = A->n;
     if (n == 0) return SRW_OK;
     double* ratio = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&ratio, n * sizeof(double), s));
+    SRW_HIP(dev_alloc((void**)&ratio, n * sizeof(double)));
     const int g = grid_for(n, BLOCK);
     k_excess_ratio<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, ratio);
     k_features<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, rank, ratio, feat);
     hipError_t e = hipGetLastError();
-    (void)hipFreeAsync(ratio, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ratio);
     SRW_HIP(e);
     return SRW_OK;
 }
@@ -537,6 +539,23 @@ __global__ void k_check_rows(int64_t n, const int32_t* __restrict__ rows, int64_
     if (i < n && (rows[i] < 0 || (int64_t)rows[i] >= n_rows)) *bad = 1;
 }
 
+// The training and scaling steps do not synchronise, so their workspaces come from the
+// stream-ordered allocator; its pool keeps up to 64 MB between them (else each step would
+// map its workspace anew).
+static void keep_stream_pool()
+{
+    static std::atomic<bool> done[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || done[dev].load()) return;
+    hipMemPool_t pool = nullptr;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess && pool) {
+        uint64_t have = 0, keep = 64ull << 20;
+        if (hipMemPoolGetAttribute(pool, hipMemPoolAttrReleaseThreshold, &have) == hipSuccess && have < keep)
+            (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+    }
+    done[dev].store(true);
+}
+
 int mlp_train_impl(float* P, float* m, float* v, int32_t step, float lr, const float* musd,
                    const float* feat, const float* target, const int32_t* rows, int64_t n_rows,
                    int64_t n, float* grad, float* loss, hipStream_t s)
@@ -545,15 +564,16 @@ int mlp_train_impl(float* P, float* m, float* v, int32_t step, float lr, const f
     if (rows) {  // the list is checked before any training work is queued
         int* bad = nullptr;
         int hbad = 0;
-        SRW_HIP(hipMallocAsync((void**)&bad, sizeof(int), s));
+        SRW_HIP(dev_alloc((void**)&bad, sizeof(int)));
         hipError_t e = hipMemsetAsync(bad, 0, sizeof(int), s);
         if (e == hipSuccess) {
             k_check_rows<<<grid_for(n, BLOCK), BLOCK, 0, s>>>(n, rows, n_rows, bad);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        (void)hipFreeAsync(bad, s);
+        const hipError_t es = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = es;
+        dev_release(bad);
         SRW_HIP(e);
         if (hbad) return SRW_E_ARG;
     } else {
@@ -562,6 +582,7 @@ int mlp_train_impl(float* P, float* m, float* v, int32_t step, float lr, const f
     const int grid = mlp_grid(n);
     const int64_t nparts = std::min<int64_t>((int64_t)grid * (BLOCK / 64), (n + 15) / 16);
     float* part = nullptr;
+    keep_stream_pool();
     SRW_HIP(hipMallocAsync((void**)&part, nparts * PART * sizeof(float), s));
     const float inv = 1.0f / (float)n;
     k_mlp_grad<<<grid, BLOCK, 0, s>>>(P, musd, feat, target, rows, n_rows, n, inv, part);
@@ -669,7 +690,7 @@ int budget_targets_impl(const double* label, const float* feat, int64_t n, int h
     char* ws = nullptr;
     const size_t o_pos = ((size_t)n * 4 + 255) & ~(size_t)255;
     const size_t o_tmp = o_pos + (((size_t)(n + 1) * 8 + 255) & ~(size_t)255);
-    SRW_HIP(hipMallocAsync((void**)&ws, o_tmp + tb + 256, s));
+    SRW_HIP(dev_alloc((void**)&ws, o_tmp + tb + 256));
     int32_t* flag = (int32_t*)ws;
     int64_t* pos = (int64_t*)(ws + o_pos);
     const unsigned g = (unsigned)grid_for(n, BLOCK);
@@ -684,8 +705,9 @@ int budget_targets_impl(const double* label, const float* feat, int64_t n, int h
     int32_t lastf[1] = {0};
     if (e == hipSuccess) e = hipMemcpyAsync(last, pos + n - 1, 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(lastf, flag + n - 1, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFreeAsync(ws, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ws);
     SRW_HIP(e);
     *count = last[0] + lastf[0];
     return SRW_OK;
@@ -695,6 +717,7 @@ int mlp_standardize_impl(const float* feat, const float* target, int64_t n, floa
                          float* target_mean, hipStream_t s)
 {
     double* ws = nullptr;
+    keep_stream_pool();
     SRW_HIP(hipMallocAsync((void**)&ws, (STD_BLOCKS * NS + NF) * sizeof(double), s));
     double* mean = ws + STD_BLOCKS * NS;
     const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(STD_BLOCKS, (n + BLOCK - 1) / BLOCK));

@@ -1225,7 +1225,7 @@ int adaptive_impl(const srw_csr* A, uint64_t seed, const srw_options* opt_in, do
     int32_t *target = nullptr, *budget = nullptr, *found = nullptr;
     int* open = nullptr;
     int* host_open = nullptr;
-    hipError_t e = hipMallocAsync((void**)&target, 3 * n * sizeof(int32_t) + 256, s);
+    hipError_t e = dev_alloc((void**)&target, 3 * n * sizeof(int32_t) + 256);
     if (e != hipSuccess) return hip_fail(e, "adaptive budgets: workspace");
     budget = target + n;
     found = budget + n;
@@ -1256,23 +1256,10 @@ int adaptive_impl(const srw_csr* A, uint64_t seed, const srw_options* opt_in, do
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess || *host_open == 0) break;
     }
-    (void)hipFreeAsync(target, s);
     (void)hipStreamSynchronize(s);
+    dev_release(target);
     if (e != hipSuccess) return hip_fail(e, "adaptive budgets");
     return status;
-}
-
-void retain_pool_memory()
-{
-    static bool done[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64 || done[dev]) return;
-    hipMemPool_t pool = nullptr;
-    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess && pool) {
-        uint64_t keep_all = UINT64_MAX;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep_all);
-    }
-    done[dev] = true;
 }
 
 int hip_fail(hipError_t e, const char* what)
@@ -1287,13 +1274,11 @@ void free_factor(srw_factor* F)
 {
     if (!F) return;
     free_factor(F->tgame);
-    for (void* p : F->allocations) (void)hipFree(p);
-    if (!F->pool_allocations.empty()) {
-        // back to the pool once the device is idle (the caller guarantees no work on F
-        // is pending; the synchronization is what hipFree would have done)
+    if (!F->allocations.empty()) {
+        // the caller guarantees that no work on F is queued after this call; what is
+        // pending must be over before the blocks can serve others
         (void)hipDeviceSynchronize();
-        for (void* p : F->pool_allocations) (void)hipFreeAsync(p, nullptr);
-        (void)hipStreamSynchronize(nullptr);
+        for (void* p : F->allocations) dev_release(p);
     }
     if (F->host_scalars) (void)hipHostFree(F->host_scalars);
     delete F;
@@ -1308,7 +1293,7 @@ int ordering_impl(int64_t n, uint64_t seed, int32_t* rank, hipStream_t s)
     const size_t bytes = 2 * align(nn * sizeof(uint64_t)) + 3 * align(nn * sizeof(uint32_t)) +
                          radix_tmp_bytes(n);
     char* ws = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&ws, bytes, s));
+    SRW_HIP(dev_alloc((void**)&ws, bytes));
     char* p = ws;
     uint64_t* keys = (uint64_t*)p; p += align(nn * sizeof(uint64_t));
     uint64_t* keys2 = (uint64_t*)p; p += align(nn * sizeof(uint64_t));
@@ -1326,8 +1311,9 @@ int ordering_impl(int64_t n, uint64_t seed, int32_t* rank, hipStream_t s)
         k_rank_scatter<<<g, BLOCK, 0, s>>>(n, vo, rank, by_rank);
         e = hipGetLastError();
     }
-    (void)hipFreeAsync(ws, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ws);
     SRW_HIP(e);
     return SRW_OK;
 }
@@ -1367,12 +1353,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
     F->precision = opt.factor_precision;
     F->keep = opt.keep;
     Arena keep;  // blocks that end up owned by F
-    Arena tmp;   // build temporaries, from the stream-ordered pool
-    retain_pool_memory();
-    tmp.pooled = true;
-    tmp.stream = s;
-    keep.pooled = true;  // the factor's blocks too: repeated builds reuse pooled memory
-    keep.stream = s;
+    Arena tmp;   // build temporaries
     // shared chunks sized to the matrix: a few n-length arrays each
     keep.chunk = std::max<size_t>((size_t)1 << 20, ((size_t)std::max<int64_t>(n, 1) * 32 + 255) & ~(size_t)255);
     tmp.chunk = 4 * keep.chunk;
@@ -1491,7 +1472,24 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         int32_t bucketing = 1;
         int64_t n_lines = 0;
         int32_t* anyb = ALLOC(tmp, int32_t, 1);
-        if (!anyb) FAIL(SRW_E_NOMEM);
+        // near records where the matrix has them (not for the walk kernels that read
+        // lines: walk reuse, refill periods below 8)
+        const int32_t nlist = batch ? batch->nmat : 1;
+        const bool near_try = !reuse && opt.refill_period == 8 && nlist <= NEAR_MATS && n > 0 &&
+                              n < ((int64_t)1 << 30);
+        int32_t* delta = ALLOC(tmp, int32_t, nlist * NEAR_DELTAS);
+        int32_t* farp = ALLOC(tmp, int32_t, 1);
+        int32_t far = 0;
+        if (!anyb || !delta || !farp) FAIL(SRW_E_NOMEM);
+        if (near_try) {
+            k_fill_i32v<<<grid_for(nlist * NEAR_DELTAS, BLOCK), BLOCK, 0, s>>>(
+                nlist * NEAR_DELTAS, delta, NO_DELTA);
+            k_fill_i32v<<<1, 1, 0, s>>>(1, farp, 0);
+            k_near_deltas<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, batch ? batch->node_mat : nullptr,
+                                              delta, farp);
+            CHECK_HIP(hipGetLastError());
+            CHECK_HIP(hipMemcpyAsync(&pinned[2], farp, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        }
         for (;;) {
             CHECK_HIP(hipMemsetAsync(anyb, 0, sizeof(int32_t), s));
             k_rec_lines<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, bucketing, nlines, kbv,
@@ -1504,6 +1502,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             n_lines = pinned[0];
             int32_t any = 0;
             std::memcpy(&any, &pinned[1], sizeof(int32_t));
+            if (near_try) std::memcpy(&far, &pinned[2], sizeof(int32_t));
             if (!bucketing || n_lines <= (int64_t)LINE_MASK) {
                 bucketing = bucketing && any;  // the walk kernel decodes line words only then
                 break;
@@ -1511,26 +1510,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             bucketing = 0;
         }
         if (2 * n_lines >= (int64_t)UINT32_MAX) FAIL(SRW_E_ARG);  // line indices are 32-bit
-        // near records where the matrix has them (not for the walk kernels that read
-        // lines: walk reuse, refill periods below 8)
-        const int32_t nlist = batch ? batch->nmat : 1;
-        bool near = !reuse && opt.refill_period == 8 && nlist <= NEAR_MATS && n > 0 &&
-                    n_lines == n && n < ((int64_t)1 << 30);
-        int32_t* delta = nullptr;
-        if (near) {
-            delta = ALLOC(tmp, int32_t, nlist * NEAR_DELTAS);
-            if (!delta) FAIL(SRW_E_NOMEM);
-            k_fill_i32v<<<grid_for(nlist * NEAR_DELTAS, BLOCK), BLOCK, 0, s>>>(
-                nlist * NEAR_DELTAS, delta, NO_DELTA);
-            CHECK_HIP(hipMemsetAsync(anyb, 0, sizeof(int32_t), s));
-            k_near_deltas<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, batch ? batch->node_mat : nullptr,
-                                              delta, anyb);
-            CHECK_HIP(hipMemcpyAsync(&pinned[1], anyb, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            CHECK_HIP(hipStreamSynchronize(s));
-            int32_t far = 0;
-            std::memcpy(&far, &pinned[1], sizeof(int32_t));
-            near = far == 0;
-        }
+        const bool near = near_try && far == 0 && n_lines == n;
         // walk records, then start records of the same shape
         const int64_t rec_words = near ? 2 * n * (NEAR_WORDS / 4) : 2 * n_lines * 4;
         uint4* recs = ALLOC(tmp, uint4, rec_words);
@@ -2213,7 +2193,7 @@ done:
         F->tsteps = nullptr; F->tvsq = nullptr; F->hlen = nullptr;
         F->h_end = nullptr; F->h_cnt = nullptr;
     }
-    F->pool_allocations = std::move(keep.blocks);
+    F->allocations = std::move(keep.blocks);
     *out = F;
     return SRW_OK;
 }

@@ -30,7 +30,7 @@ namespace srw {
 int hip_fail(hipError_t e, const char* what);
 // Small pinned host block of this thread (32 int64), allocated on first use and kept
 // until the process ends; nullptr if the allocation failed.  Slots: [0, 8) the build,
-// [8, 12) the solvers, [16] the adaptive budget rounds.
+// [8, 12) the solvers, [16] the adaptive budget rounds, [20, 28) the batched solves.
 int64_t* host_scratch();
 void set_last_error(const char* msg);
 // Ticks of the device's constant-rate wall clock (wall_clock64) in `seconds`, for the

@@ -93,8 +93,7 @@ struct srw_factor {
     double* scalars = nullptr;
     double* host_scalars = nullptr;  // pinned
 
-    std::vector<void*> allocations;       // device blocks owned by this factor (hipMalloc)
-    std::vector<void*> pool_allocations;  // ... from the stream-ordered pool (hipMallocAsync)
+    std::vector<void*> allocations;  // device blocks owned by this factor (dev_alloc)
 };
 
 namespace srw {
@@ -105,17 +104,18 @@ constexpr int64_t HEAD_DEFAULT = 4096;
 // times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.6 ms)
 constexpr int64_t HEAD_COST = (int64_t)8 << 30;
 
-// Device allocation tracked by an owner list (freed together).  With a stream the
-// blocks come from the stream-ordered pool (hipMallocAsync / hipFreeAsync), so the
-// temporaries of repeated builds reuse pooled memory instead of being mapped anew.
-// With a chunk size, requests up to half a chunk are carved out of shared chunks
-// (256-byte aligned), larger ones get a block of their own: each runtime allocation
-// and free costs tens to hundreds of microseconds, so a build makes few of them.
+// Device memory from the library's kept blocks (pool.cpp).  dev_release: no work on the
+// block may be pending (the caller has synchronised); it may be called from any thread.
+// dev_trim gives every kept block back to the device.
+hipError_t dev_alloc(void** out, size_t bytes);
+void dev_release(void* p);
+void dev_trim(int dev);
+
+// Device allocations tracked by an owner list (released together).  With a chunk size, requests up to half a chunk are carved out of shared chunks
+// (256-byte aligned), larger ones get a block of their own.
 struct Arena {
     std::vector<void*> blocks;
     hipError_t last = hipSuccess;
-    hipStream_t stream = nullptr;
-    bool pooled = false;
     size_t chunk = 0;    // 0: every request is a block of its own
     char* cur = nullptr;  // free tail of the current chunk
     size_t left = 0;
@@ -132,7 +132,7 @@ struct Arena {
         const bool own = bytes > chunk / 2;
         const size_t size = own ? bytes : chunk;
         void* p = nullptr;
-        hipError_t e = pooled ? hipMallocAsync(&p, size, stream) : hipMalloc(&p, size);
+        const hipError_t e = dev_alloc(&p, size);
         if (e != hipSuccess) {
             last = e;
             return nullptr;
@@ -146,16 +146,12 @@ struct Arena {
     }
     void release()
     {
-        for (void* p : blocks) (void)(pooled ? hipFreeAsync(p, stream) : hipFree(p));
+        for (void* p : blocks) dev_release(p);
         blocks.clear();
         cur = nullptr;
         left = 0;
     }
 };
-
-// Keeps freed stream-ordered allocations in the device's default pool (release
-// threshold raised once per device), so they are reused by the next build.
-void retain_pool_memory();
 
 // Walk keys of a batched build: the matrix of every node of the block-diagonal
 // matrix, the first node of every matrix and the matrix's seed.

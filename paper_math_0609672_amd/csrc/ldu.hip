@@ -244,10 +244,10 @@ int build_ldu_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uin
     const size_t bytes = 2 * align(m * sizeof(uint64_t)) + 3 * align(m * sizeof(uint32_t)) +
                          align((size_t)(n + 1) * sizeof(int64_t)) + align(m * sizeof(int32_t)) +
                          align(m * sizeof(double)) + radix_tmp_bytes(nnz);
-    hipError_t e = hipMallocAsync((void**)&ws, bytes, s);
+    hipError_t e = dev_alloc((void**)&ws, bytes);
     if (e != hipSuccess) {
         free_factor(F);
-        return hip_fail(e, "hipMallocAsync");
+        return hip_fail(e, "transpose workspace");
     }
     char* p = ws;
     uint64_t* key = (uint64_t*)p; p += align(m * sizeof(uint64_t));
@@ -274,7 +274,8 @@ int build_ldu_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uin
         e = hipGetLastError();
     }
     if (e != hipSuccess) {
-        (void)hipFreeAsync(ws, s);
+        (void)hipStreamSynchronize(s);
+        dev_release(ws);
         free_factor(F);
         return hip_fail(e, "transpose");
     }
@@ -285,8 +286,8 @@ int build_ldu_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uin
     ot.rank = F->rank;
     srw_factor* G = nullptr;
     st = build_factor_impl(&At, walks_per_row, drop_tol, seed, &ot, &G, s, nullptr, nullptr, true);
-    (void)hipFreeAsync(ws, s);
     (void)hipStreamSynchronize(s);
+    dev_release(ws);
     if (st != SRW_OK) {
         free_factor(F);
         return st;
@@ -304,7 +305,7 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
     double* ws = nullptr;
     // r, rt, p, v, ph, s, sh, t, 2 n of preconditioner scratch, partials, sums, err
-    SRW_HIP(hipMallocAsync((void**)&ws, (10 * vec + 2 * RED + 4) * sizeof(double), s));
+    SRW_HIP(dev_alloc((void**)&ws, (10 * vec + 2 * RED + 4) * sizeof(double)));
     double *r = ws, *rt = ws + vec, *p = ws + 2 * vec, *v = ws + 3 * vec, *ph = ws + 4 * vec;
     double *sv = ws + 5 * vec, *sh = ws + 6 * vec, *t = ws + 7 * vec, *work = ws + 8 * vec;
     double* part = ws + 10 * vec;
@@ -314,7 +315,7 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
     host = host_scratch() ? (double*)(host_scratch() + 8) : nullptr;
     hipError_t e = host ? hipSuccess : hipErrorOutOfMemory;
     if (e != hipSuccess) {
-        (void)hipFreeAsync(ws, s);
+        dev_release(ws);
         return hip_fail(e, "hipHostMalloc");
     }
     int status = SRW_NOT_CONVERGED;
@@ -434,8 +435,8 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
     }
 out:
 #undef STEP
-    (void)hipFreeAsync(ws, s);
     (void)hipStreamSynchronize(s);
+    dev_release(ws);
     if (iters_out) *iters_out = it;
     if (rel_out) *rel_out = rel;
     if (gave_up) {

@@ -779,15 +779,15 @@ int apply_impl(srw_factor* F, const double* r, double* z, hipStream_t s)
     const int64_t n = F->n;
     char* ws = nullptr;
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
-    SRW_HIP(hipMallocAsync((void**)&ws, 2 * vec * sizeof(double) + 64, s));
+    SRW_HIP(dev_alloc((void**)&ws, 2 * vec * sizeof(double) + 64));
     int* err = (int*)(ws + 2 * vec * sizeof(double));
     hipError_t e = hipMemsetAsync(err, 0, sizeof(int), s);
     if (e == hipSuccess) e = apply_any(F, r, ws, z, err, s);
     int herr = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFreeAsync(ws, s);
-    (void)hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ws);
     SRW_HIP(e);
     return herr ? SRW_E_HIP : SRW_OK;
 }
@@ -858,7 +858,7 @@ int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
     *depth_out = 0;
     if (n == 0) return SRW_OK;
     char* ws = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&ws, 64, s));
+    SRW_HIP(dev_alloc((void**)&ws, 64));
     int* depth = (int*)ws;
     int* err = depth + 1;
     hipError_t e = hipMemsetAsync(depth, 0, 2 * sizeof(int), s);
@@ -875,9 +875,9 @@ int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
     }
     int host[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(host, depth, 2 * sizeof(int), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFreeAsync(ws, s);
-    (void)hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    dev_release(ws);
     SRW_HIP(e);
     if (host[1]) return SRW_E_HIP;
     *depth_out = host[0];
@@ -890,10 +890,10 @@ int dag_depth(srw_factor* F, int32_t* depth_out, hipStream_t s)
     *depth_out = 0;
     if (n == 0) return SRW_OK;
     int32_t* lev = nullptr;
-    SRW_HIP(hipMallocAsync((void**)&lev, n * sizeof(int32_t), s));
+    SRW_HIP(dev_alloc((void**)&lev, n * sizeof(int32_t)));
     const int st = dag_levels(F, lev, depth_out, s);
-    (void)hipFreeAsync(lev, s);
     (void)hipStreamSynchronize(s);
+    dev_release(lev);
     return st;
 }
 
@@ -906,7 +906,7 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
     double* ws = nullptr;
     double* host = nullptr;
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
-    SRW_HIP(hipMallocAsync((void**)&ws, (6 * vec + RED_GRID + S_COUNT + 4) * sizeof(double), s));
+    SRW_HIP(dev_alloc((void**)&ws, (6 * vec + RED_GRID + S_COUNT + 4) * sizeof(double)));
     double *r = ws, *z = ws + vec, *p = ws + 2 * vec, *q = ws + 3 * vec, *work = ws + 4 * vec;
     double* partials = ws + 6 * vec;
     double* sc = partials + RED_GRID;
@@ -914,7 +914,7 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
     host = host_scratch() ? (double*)(host_scratch() + 8) : nullptr;
     hipError_t herr = host ? hipSuccess : hipErrorOutOfMemory;
     if (herr != hipSuccess) {
-        (void)hipFreeAsync(ws, s);
+        dev_release(ws);
         return hip_fail(herr, "hipHostMalloc");
     }
     int status = SRW_NOT_CONVERGED;
@@ -1007,8 +1007,8 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
     }
 out:
 #undef STEP
-    (void)hipFreeAsync(ws, s);
     (void)hipStreamSynchronize(s);
+    dev_release(ws);
     if (gave_up) {
         set_last_error("pcg: a triangular solve gave up waiting, or the residual is not finite");
         return SRW_E_HIP;
