@@ -147,6 +147,38 @@ __device__ __forceinline__ uint32_t threshold32(double c, double d)
     return (uint32_t)x;
 }
 
+// Row i of a CSR matrix times x, for the workgroup's 256 consecutive rows at `base` (thread
+// t: row base + t; all threads call it).  The products are made in entry order, 2,048 at a
+// time, by consecutive threads, and each thread then adds its row's from LDS, first entry
+// first, as a loop over the row would: the same sums.  A thread that reads its own row
+// alone touches a cache line per entry: on 2M rows at degree 24 (51M entries) 2,210 us
+// with the sums of a conjugate gradient step, 704 us this way (the entries take 140 us at
+// the rate of a copy, the gathers of x the rest); 70 us either way on the grid 128^3.
+constexpr int ROWS_TILE = 2048;
+
+__device__ __forceinline__ double row_times(int64_t base, int64_t n, const int64_t* __restrict__ rowptr,
+                                            const int32_t* __restrict__ col,
+                                            const double* __restrict__ val,
+                                            const double* __restrict__ x, double* prod)
+{
+    const int tid = threadIdx.x;
+    const int64_t i = base + tid;
+    const int64_t r0 = i < n ? rowptr[i] : 0, r1 = i < n ? rowptr[i + 1] : 0;
+    const int64_t e0 = rowptr[base], e1 = rowptr[base + 256 < n ? base + 256 : n];
+    double acc = 0.0;
+    for (int64_t t0 = e0; t0 < e1; t0 += ROWS_TILE) {
+        const int m = (int)(e1 - t0 < ROWS_TILE ? e1 - t0 : ROWS_TILE);
+#pragma unroll
+        for (int k = 0; k < ROWS_TILE; k += 256)
+            if (k + tid < m) prod[k + tid] = val[t0 + k + tid] * x[col[t0 + k + tid]];
+        __syncthreads();
+        const int64_t lo = r0 > t0 ? r0 : t0, hi = r1 < t0 + m ? r1 : t0 + m;
+        for (int64_t e = lo; e < hi; ++e) acc += prod[e - t0];
+        __syncthreads();
+    }
+    return acc;
+}
+
 // ------------------------------------------------------------- device algorithms
 // (implemented in scan_sort.hip)
 // Exclusive prefix sum of n int64 values (in may alias out).  tmp: scan_tmp_bytes(n).

@@ -90,11 +90,10 @@ __global__ __launch_bounds__(BLOCK) void k_spmv(int64_t n, const int64_t* __rest
                                                 const double* __restrict__ val,
                                                 const double* __restrict__ x, double* __restrict__ y)
 {
-    GRID_STRIDE(i, n)
-    {
-        double acc = 0.0;
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) acc += val[e] * x[col[e]];
-        y[i] = acc;
+    __shared__ double prod[ROWS_TILE];
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
+        const double acc = row_times(base, n, rowptr, col, val, x, prod);
+        if (base + threadIdx.x < n) y[base + threadIdx.x] = acc;
     }
 }
 
@@ -199,14 +198,16 @@ __global__ __launch_bounds__(BLOCK) void k_bicg_residual(int64_t n, const int64_
                                                          double* __restrict__ r, double* part)
 {
     __shared__ double lds[BLOCK / 64];
+    __shared__ double prod[ROWS_TILE];
     double acc = 0.0;
-    GRID_STRIDE(i, n)
-    {
-        double q = 0.0;
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) q += val[e] * x[col[e]];
-        const double ri = b[i] - q;
-        r[i] = ri;
-        acc += ri * ri;
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
+        const double q = row_times(base, n, rowptr, col, val, x, prod);
+        const int64_t i = base + threadIdx.x;
+        if (i < n) {
+            const double ri = b[i] - q;
+            r[i] = ri;
+            acc += ri * ri;
+        }
     }
     acc = block_sum(acc, lds);
     if (threadIdx.x == 0) part[blockIdx.x] = acc;

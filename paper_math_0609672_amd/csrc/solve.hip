@@ -18,7 +18,7 @@ namespace srw {
 
 namespace {
 
-constexpr int BLOCK = 256;
+constexpr int BLOCK = 256;  // (row_times takes 256 rows)
 constexpr int RED_GRID = 1024;  // blocks of every reducing kernel (grid-stride)
 
 enum Scalar : int { S_RHO = 0, S_PQ, S_ALPHA, S_RR, S_RHO_NEW, S_BETA, S_BB, S_COUNT };
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(BLOCK) void k_finalize(const double* __restrict__ p
     }
 }
 
-// q = A p (one thread per row, entries in CSR order) and partials of p . q
+// q = A p (every row's entries added in CSR order) and partials of p . q
 __global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, const int64_t* __restrict__ rowptr,
                                                     const int32_t* __restrict__ col,
                                                     const double* __restrict__ val,
@@ -80,12 +80,15 @@ __global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, const int64_t* __
                                                     double* __restrict__ q, double* partials)
 {
     __shared__ double lds[BLOCK / 64];
+    __shared__ double prod[ROWS_TILE];
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) {
-        double acc = 0.0;
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) acc += val[e] * p[col[e]];
-        q[i] = acc;
-        s += p[i] * acc;
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
+        const double acc = row_times(base, n, rowptr, col, val, p, prod);
+        const int64_t i = base + threadIdx.x;
+        if (i < n) {
+            q[i] = acc;
+            s += p[i] * acc;
+        }
     }
     s = block_sum(s, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
@@ -100,13 +103,16 @@ __global__ __launch_bounds__(BLOCK) void k_residual(int64_t n, const int64_t* __
                                                     double* __restrict__ r, double* partials)
 {
     __shared__ double lds[BLOCK / 64];
+    __shared__ double prod[ROWS_TILE];
     double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) {
-        double acc = 0.0;
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) acc += val[e] * x[col[e]];
-        const double ri = b[i] - acc;
-        r[i] = ri;
-        s += ri * ri;
+    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
+        const double acc = row_times(base, n, rowptr, col, val, x, prod);
+        const int64_t i = base + threadIdx.x;
+        if (i < n) {
+            const double ri = b[i] - acc;
+            r[i] = ri;
+            s += ri * ri;
+        }
     }
     s = block_sum(s, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
