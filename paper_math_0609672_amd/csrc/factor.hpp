@@ -47,6 +47,9 @@ struct srw_factor {
     // by rows (row i: X[i][0..i] at i(i+1)/2), and its transpose packed by rows (row j:
     // X[j..head-1][j] at j head - j(j-1)/2)
     int64_t head = 0;
+    // the slots before this one hold most of the solves' dependency chain and are
+    // substituted by a launch of their own (n: one launch for all)
+    int64_t chain_end = 0;
     void* hx = nullptr;
     void* hxt = nullptr;
 

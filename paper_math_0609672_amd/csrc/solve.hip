@@ -169,10 +169,10 @@ __global__ __launch_bounds__(BLOCK) void k_copy(int64_t n, const double* __restr
 // row's dependencies are all done, so the solve always progresses.  The solution
 // starts filled with a signalling-NaN pattern that arithmetic never produces; a
 // row's value is published with one device-scope store and is its own ready flag.
-// A waiting wave polls one address only -- that of its missing dependency which the
+// A waiting row polls mostly one address -- that of its missing dependency which the
 // order solves last -- and once that one is there reloads its other missing values,
 // if any.
-// The lane partial sums are added by a wave-wide butterfly, so the result does not
+// The lane partial sums are added by a butterfly over the row's lanes, so the result does not
 // depend on timing.
 template <typename T>
 struct Bits;
@@ -203,6 +203,7 @@ struct Bits<int32_t> {
 #ifndef SRW_POLL_SLEEP
 #define SRW_POLL_SLEEP 2  // s_sleep units (64 clocks) between polls of a missing value
 #endif
+constexpr uint32_t POLL_OTHERS = 4;  // polls of the lead between those of the others
 
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_fill_sentinel(int64_t n, T* x)
@@ -267,10 +268,71 @@ __device__ __forceinline__ void wait_published(typename Bits<T>::U& bits, const 
     }
 }
 
-// The substitution covers the slots h..n-1 (the first h slots are the dense head, done
-// by the head kernels: before the forward rows, after the backward ones).
-template <typename T, bool FWD>
-__global__ __launch_bounds__(BLOCK) void k_trsv(int64_t n, int64_t h, const int64_t* __restrict__ ptr,
+// One VALU move across the lanes of a row of 16 (CTRL: the DPP control word).
+template <int CTRL, typename V>
+__device__ __forceinline__ V dpp_move(V x)
+{
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+        return __builtin_bit_cast(V, ((uint64_t)hi << 32) | lo);
+    } else {
+        return __builtin_bit_cast(V, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+    }
+}
+
+// The value D lanes away (D = 16, 32: rows of 16, halves of the wave change places).
+template <int D, typename V>
+__device__ __forceinline__ V row_swap(V x)
+{
+    auto swap32 = [](uint32_t u) -> uint32_t {
+        const auto r = D == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                               : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return ((__lane_id() & D) != 0) ? (uint32_t)r[0] : (uint32_t)r[1];
+    };
+    if constexpr (sizeof(V) == 8) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, x);
+        return __builtin_bit_cast(V, ((uint64_t)swap32((uint32_t)(u >> 32)) << 32) | swap32((uint32_t)u));
+    } else {
+        return __builtin_bit_cast(V, swap32(__builtin_bit_cast(uint32_t, x)));
+    }
+}
+
+// f over the LPR lanes of a row group, the same result in all of them: partners one and
+// two lanes away, then the mirrored half rows and rows of 16 lanes, then 16 and 32 away.
+template <int LPR, typename V, typename F>
+__device__ __forceinline__ V group_reduce(V x, F f)
+{
+    x = f(x, dpp_move<0xB1>(x));   // quad_perm [1, 0, 3, 2]
+    x = f(x, dpp_move<0x4E>(x));   // quad_perm [2, 3, 0, 1]
+    x = f(x, dpp_move<0x141>(x));  // row_half_mirror
+    x = f(x, dpp_move<0x140>(x));  // row_mirror
+    if constexpr (LPR >= 32) x = f(x, row_swap<16>(x));
+    if constexpr (LPR >= 64) x = f(x, row_swap<32>(x));
+    return x;
+}
+
+// The substitution over the slots lo..hi-1.
+//
+// LPR lanes take a row, so a wave has 64 / LPR consecutive rows of the order in flight,
+// ROW_U entries a lane at first.  Rows hold about 20 entries on 3D grids and 90 on the
+// geometric graph: a wave per row leaves two thirds of its lanes idle, and its rows, taken
+// one after the other, are what the solve waits for where the levels are wide.  The
+// rows of a wave wait and finish each for itself (one may wait for another).  Bounds and
+// node of the row after the next, entries and right-hand side of the next row are loaded
+// while a row waits.  A value is first read through the caches, which may still hold the
+// sentinel after it was published, never anything older; only then past them.  The other
+// missing values are read again on every fourth poll (128^3, one application, us: on every
+// poll 3,702, every second 3,323, every fourth 3,161, every sixteenth no better): the poll
+// traffic slows the values it waits for.  One application, in us, a wave per row in one
+// launch before and this way: 128^3 3,596 and 2,858; geometric graph of 2M nodes 9,074 and
+// 8,150; 64^3 1,211 and 1,062; 2D grid of 490,000 674 and 626.
+constexpr int ROW_U = 2;
+
+template <typename T, bool FWD, int LPR>
+__global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
+                                                const int64_t* __restrict__ ptr,
                                                 const int32_t* __restrict__ col,
                                                 const T* __restrict__ val,
                                                 const T* __restrict__ dslot,
@@ -281,62 +343,172 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t n, int64_t h, const int6
                                                 int64_t ticks)
 {
     using U = typename Bits<T>::U;
+    constexpr int G = 64 / LPR;
+    constexpr uint64_t GMASK = LPR == 64 ? ~0ull : (1ull << LPR) - 1ull;
     const int lane = threadIdx.x & 63;
+    const int grp = lane / LPR, gl = lane % LPR;
     const int64_t nw = (int64_t)gridDim.x * (BLOCK / 64);
     const int64_t wid =
         (int64_t)blockIdx.x * (BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t m = n - h;  // rows substituted
-    if (wid >= m) return;  // whole wave
-    // the wave's next row, loaded one row ahead: bounds and first 64 entries
-    int64_t s = FWD ? h + wid : n - 1 - wid;
-    int64_t q0 = ptr[s], q1 = ptr[s + 1];
-    int32_t c = 0;
-    T v = T(0);
-    if (q0 + lane < q1) {
-        c = col[q0 + lane];
-        v = val[q0 + lane];
+    const int64_t m = hi - lo;  // rows substituted
+    if (wid * G >= m) return;  // whole wave
+    const int64_t step = nw * G;
+    auto slot = [&](int64_t i) { return FWD ? lo + i : hi - 1 - i; };
+    // row i (this one), i + step (b: bounds and node known) and i + 2 step (a)
+    int64_t i = wid * G + grp;
+    int64_t q0 = 0, q1 = 0, bq0 = 0, bq1 = 0;
+    int32_t node = 0, bnode = 0;
+    int32_t c[ROW_U];
+    T v[ROW_U], base = T(0);
+    if (i < m) {
+        q0 = ptr[slot(i)];
+        q1 = ptr[slot(i) + 1];
+        node = slot_node[slot(i)];
+        base = FWD ? w[slot(i)] / dslot[slot(i)] : (T)rhs[node];
     }
-    for (int64_t i = wid; i < m; i += nw) {
-        const bool valid = q0 + lane < q1;
-        U bits = valid ? load_published((const U*)sol + c) : U(0);
-        const int32_t node = slot_node[s];
-        const T base = FWD ? w[s] / dslot[s] : (T)rhs[node];
-        const int64_t i2 = i + nw;
-        int64_t s2 = 0, p0 = 0, p1 = 0;
-        int32_t c2 = 0;
-        T v2 = T(0);
-        if (i2 < m) {
-            s2 = FWD ? h + i2 : n - 1 - i2;
-            p0 = ptr[s2];
-            p1 = ptr[s2 + 1];
-            if (p0 + lane < p1) {
-                c2 = col[p0 + lane];
-                v2 = val[p0 + lane];
+    if (i + step < m) {
+        bq0 = ptr[slot(i + step)];
+        bq1 = ptr[slot(i + step) + 1];
+        bnode = slot_node[slot(i + step)];
+    }
+#pragma unroll
+    for (int k = 0; k < ROW_U; ++k) {
+        const int64_t q = q0 + k * LPR + gl;
+        c[k] = q < q1 ? col[q] : 0;
+        v[k] = q < q1 ? val[q] : T(0);
+    }
+    for (int64_t i0 = wid * G; i0 < m; i0 += step, i += step) {
+        // the values of this row's first entries
+        U bits[ROW_U];
+#pragma unroll
+        for (int k = 0; k < ROW_U; ++k)
+            bits[k] = q0 + k * LPR + gl < q1
+                          ? __hip_atomic_load((const U*)sol + c[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                          : U(0);
+        // the next row's entries and right-hand side, the bounds of the one after it
+        int32_t nc[ROW_U];
+        T nv[ROW_U];
+        int64_t aq0 = 0, aq1 = 0;
+        int32_t anode = 0;
+#pragma unroll
+        for (int k = 0; k < ROW_U; ++k) {
+            const int64_t q = bq0 + k * LPR + gl;
+            nc[k] = q < bq1 ? col[q] : 0;
+            nv[k] = q < bq1 ? val[q] : T(0);
+        }
+        T nw_ = T(0), nd = T(1);
+        if (i + step < m) {
+            if (FWD) {
+                nw_ = w[slot(i + step)];
+                nd = dslot[slot(i + step)];
+            } else {
+                nw_ = (T)rhs[bnode];
             }
         }
-        wait_published<T, FWD>(bits, c, valid, sol, err, ticks);
-        T acc = v * __builtin_bit_cast(T, bits);
-        for (int64_t qb = q0 + 64; qb < q1; qb += 64) {  // rows longer than 64 entries
-            const int64_t q = qb + lane;
-            const bool ok = q < q1;
-            const int32_t cc = ok ? col[q] : 0;
-            const T vv = ok ? val[q] : T(0);
-            U bb = ok ? load_published((const U*)sol + cc) : U(0);
-            wait_published<T, FWD>(bb, cc, ok, sol, err, ticks);
-            acc += vv * __builtin_bit_cast(T, bb);
+        if (i + 2 * step < m) {
+            aq0 = ptr[slot(i + 2 * step)];
+            aq1 = ptr[slot(i + 2 * step) + 1];
+            anode = slot_node[slot(i + 2 * step)];
         }
-        acc = wave_sum(acc);
-        if (lane == 0) {
-            const T x = base - acc;
-            __hip_atomic_store((U*)sol + s, __builtin_bit_cast(U, x), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            if (out) out[node] = (double)x;
+        bool done = i >= m;
+        int64_t qn = q0 + ROW_U * LPR;  // the row's entries past those in registers
+        T acc = T(0);
+        uint32_t spins = 0;
+        int64_t t0 = 0;
+        for (;;) {
+            bool miss = false;
+            int key = INT_MIN;  // the missing value that the order solves last
+#pragma unroll
+            for (int k = 0; k < ROW_U; ++k) {
+                const bool mk = bits[k] == Bits<T>::sentinel;
+                miss = miss || mk;
+                key = mk ? max(key, FWD ? c[k] : ~c[k]) : key;
+            }
+            miss = miss && !done;
+            const uint64_t mb = ballot(miss);
+            const bool gmiss = ((mb >> (grp * LPR)) & GMASK) != 0;
+            const bool ready = !done && !gmiss;
+            if (ready) {
+#pragma unroll
+                for (int k = 0; k < ROW_U; ++k) acc += v[k] * __builtin_bit_cast(T, bits[k]);
+                if (qn < q1) {  // a long row: its next entries
+#pragma unroll
+                    for (int k = 0; k < ROW_U; ++k) {
+                        const int64_t q = qn + k * LPR + gl;
+                        c[k] = q < q1 ? col[q] : 0;
+                        v[k] = q < q1 ? val[q] : T(0);
+                    }
+#pragma unroll
+                    for (int k = 0; k < ROW_U; ++k)
+                        bits[k] = qn + k * LPR + gl < q1
+                                      ? __hip_atomic_load((const U*)sol + c[k], __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_WORKGROUP)
+                                      : U(0);
+                }
+                qn += ROW_U * LPR;
+            }
+            const bool fin = ready && qn >= q1 + ROW_U * LPR;
+            if (ballot(fin) != 0) {
+                const T sum = group_reduce<LPR>(acc, [](T x, T y) { return x + y; });
+                if (fin) {
+                    if (gl == 0) {
+                        const T x = base - sum;
+                        __hip_atomic_store((U*)sol + slot(i), __builtin_bit_cast(U, x), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        if (out) out[node] = (double)x;
+                    }
+                    done = true;
+                }
+            }
+            if (ballot(!done) == 0) break;
+            if (mb == 0) continue;
+            if (spins == 0) t0 = wall_clock64();
+            // every 256 polls: give up past the time limit, or at once when another wave
+            // already gave up (a failed solve then drains instead of waiting at every row)
+            if ((++spins & 255u) == 0 &&
+                (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
+                 wall_clock64() - t0 > ticks)) {
+                if (lane == 0) atomicOr(err, 1);
+#pragma unroll
+                for (int k = 0; k < ROW_U; ++k)
+                    if (bits[k] == Bits<T>::sentinel) bits[k] = Bits<T>::nan_bits();
+                continue;
+            }
+            const int gk = group_reduce<LPR>(key, [](int x, int y) { return max(x, y); });
+            const int32_t lead = FWD ? gk : ~gk;
+            U lb = U(0);
+            if (gmiss) lb = load_published((const U*)sol + lead);  // one address for the group
+            // the other missing values now and then, so that most often none is left to
+            // load when the lead arrives
+            const bool others = (spins & (POLL_OTHERS - 1)) == 0;
+            U ob[ROW_U];
+#pragma unroll
+            for (int k = 0; k < ROW_U; ++k) {
+                ob[k] = bits[k];
+                if (others && gmiss && bits[k] == Bits<T>::sentinel && c[k] != lead)
+                    ob[k] = load_published((const U*)sol + c[k]);
+            }
+            const bool got = gmiss && lb != Bits<T>::sentinel;
+#pragma unroll
+            for (int k = 0; k < ROW_U; ++k) {
+                bits[k] = ob[k];
+                if (got && bits[k] == Bits<T>::sentinel)
+                    bits[k] = c[k] == lead ? lb : load_published((const U*)sol + c[k]);
+            }
+            if (ballot(got) == 0) __builtin_amdgcn_s_sleep(SRW_POLL_SLEEP);
         }
-        s = s2;
-        q0 = p0;
-        q1 = p1;
-        c = c2;
-        v = v2;
+        q0 = bq0;
+        q1 = bq1;
+        node = bnode;
+        base = FWD ? nw_ / nd : nw_;
+#pragma unroll
+        for (int k = 0; k < ROW_U; ++k) {
+            c[k] = nc[k];
+            v[k] = nv[k];
+        }
+        bq0 = aq0;
+        bq1 = aq1;
+        bnode = anode;
     }
 }
 
@@ -543,10 +715,15 @@ __global__ __launch_bounds__(BLOCK) void k_head_mv(int64_t h, const T* __restric
     }
 }
 
-// Grid of a cooperative launch: every block resident at once (occupancy x CUs),
-// capped at the blocks the work can use.
+// Workgroups per CU of the chain's launch: the rows there wait for one another, and fewer
+// waves poll less.  128^3, one application: 2 to a CU 2,870 us, 4 to a CU 2,923, all that
+// fit 3,100; geometric graph of 2M nodes: 8,141, 8,537, 8,650.
+constexpr int CHAIN_BLOCKS_PER_CU = 2;
+
+// Grid of a cooperative launch: every block resident at once (occupancy x CUs), at most
+// per_cu_cap per CU, capped at the blocks the work can use (rows: one per wave).
 template <typename K>
-hipError_t coop_launch(K kernel, int64_t rows, void** args, hipStream_t s)
+hipError_t coop_launch(K kernel, int64_t rows, void** args, hipStream_t s, int per_cu_cap = 64)
 {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -556,41 +733,65 @@ hipError_t coop_launch(K kernel, int64_t rows, void** args, hipStream_t s)
     // The waits need every wave resident at once.  The runtime's occupancy is not
     // always met in full (a kernel reported at 8 workgroups per CU was measured running
     // 7 together), so the grid leaves one workgroup in eight unused.
-    int64_t blocks = (int64_t)cus * std::max(1, per_cu * 7 / 8);
-    blocks = std::min<int64_t>(blocks, (rows + BLOCK / 64 - 1) / (BLOCK / 64));
-    if (blocks < 1) blocks = 1;
+    int64_t blocks = (int64_t)cus * std::max(1, std::min(per_cu_cap, per_cu * 7 / 8));
+    blocks = std::max<int64_t>(1, std::min<int64_t>(blocks, (rows + BLOCK / 64 - 1) / (BLOCK / 64)));
     return hipLaunchCooperativeKernel((const void*)kernel, dim3((unsigned)blocks), dim3(BLOCK),
                                       args, 0, s);
 }
 
+// Lanes per row of the wide part, by the factor's mean row length (a lane takes two
+// entries at once): 16 lanes up to 28 entries, 32 up to 56, a wave past them.
+template <typename T, bool FWD>
+hipError_t trsv_launch(const srw_factor* F, int64_t rows, bool chain, void** args, hipStream_t s)
+{
+    if (chain)  // a wave per row: the row's own latency counts
+        return coop_launch(k_trsv<T, FWD, 64>, rows, args, s, F->chain_end < F->n ? CHAIN_BLOCKS_PER_CU : 64);
+    if (F->nnz_y > 56 * F->n) return coop_launch(k_trsv<T, FWD, 64>, rows, args, s);
+    if (F->nnz_y > 28 * F->n) return coop_launch(k_trsv<T, FWD, 32>, (rows + 1) / 2, args, s);
+    return coop_launch(k_trsv<T, FWD, 16>, (rows + 3) / 4, args, s);
+}
+
 int fill_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(grid_for(n, BLOCK), 1), 2048); }
+
+// The substitution over slots h..n-1 of one triangle of the plan, in two launches: the
+// slots before chain_end hold most of the dependency chain and little work, the others
+// the work.
+template <typename T, bool FWD>
+hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T* w, T* sol, double* out,
+                      int* err, hipStream_t s)
+{
+    const int64_t n = F->n;
+    const int64_t* ptr = FWD ? F->fptr : F->bptr;
+    const int32_t* col = FWD ? F->fcol : F->bcol;
+    const T* val = (const T*)(FWD ? F->fval : F->bval);
+    const T* dslot = FWD ? (const T*)F->dslot : nullptr;
+    const int32_t* slot_node = F->slot_node;
+    int64_t ticks = wait_ticks(5.0);
+    for (int part = 0; part < 2; ++part) {
+        const bool chain = (part == 0) == FWD;
+        int64_t lo = chain ? h : F->chain_end, hi = chain ? F->chain_end : n;
+        if (lo >= hi) continue;
+        void* args[] = {&lo, &hi, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &sol, &out, &err, &ticks};
+        const hipError_t e = trsv_launch<T, FWD>(F, hi - lo, chain, args, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 // work, sol: n values of T each; z (node order) receives the result as doubles.
 template <typename T>
 hipError_t apply_plan(const srw_factor* F, const double* r, T* work, T* sol, double* z, int* err,
                       hipStream_t s)
 {
-    int64_t n = F->n;
-    int64_t h = F->head;
-    int64_t ticks = wait_ticks(5.0);
-    k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, work);
-    k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, sol);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const int64_t n = F->n;
+    const int64_t h = F->head;
+    hipError_t e = hipSuccess;
     const unsigned hg = (unsigned)((h + BLOCK / 64 - 1) / (BLOCK / 64));
     if (n > h) {
-        const int64_t* ptr = F->bptr;
-        const int32_t* col = F->bcol;
-        const T* val = (const T*)F->bval;
-        const T* dslot = nullptr;
-        const int32_t* slot_node = F->slot_node;
-        const double* rhs = r;
-        const T* w = nullptr;
-        T* out_sol = work;
-        double* out = nullptr;
-        void* args[] = {&n, &h, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &out_sol, &out, &err,
-                        &ticks};
-        e = coop_launch(k_trsv<T, false>, n - h, args, s);
+        k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, work);
+        k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, sol);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        e = substitute<T, false>(F, h, r, nullptr, work, nullptr, err, s);
         if (e != hipSuccess) return e;
     }
     if (h > 0) {
@@ -603,20 +804,7 @@ hipError_t apply_plan(const srw_factor* F, const double* r, T* work, T* sol, dou
                                                 F->slot_node, sol, z);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (n > h) {
-        const int64_t* ptr = F->fptr;
-        const int32_t* col = F->fcol;
-        const T* val = (const T*)F->fval;
-        const T* dslot = (const T*)F->dslot;
-        const int32_t* slot_node = F->slot_node;
-        const double* rhs = nullptr;
-        const T* w = work;
-        T* out_sol = sol;
-        double* out = z;
-        void* args[] = {&n, &h, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &out_sol, &out, &err,
-                        &ticks};
-        e = coop_launch(k_trsv<T, true>, n - h, args, s);
-    }
+    if (n > h) e = substitute<T, true>(F, h, nullptr, work, sol, z, err, s);
     return e;
 }
 
@@ -636,45 +824,16 @@ hipError_t apply_ldu_plan(const srw_factor* F, const double* r, T* work, T* sol,
                           int* err, hipStream_t s)
 {
     const srw_factor* G = F->tgame;
-    int64_t n = F->n;
-    int64_t h = 0;  // the games' factors take no dense head
-    int64_t ticks = wait_ticks(5.0);
+    const int64_t n = F->n;  // (the games' factors take no dense head)
     k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, work);
     k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, sol);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    {
-        const int64_t* ptr = G->bptr;
-        const int32_t* col = G->bcol;
-        const T* val = (const T*)G->bval;
-        const T* dslot = nullptr;
-        const int32_t* slot_node = G->slot_node;
-        const double* rhs = r;
-        const T* w = nullptr;
-        T* out_sol = work;
-        double* out = z;
-        void* args[] = {&n, &h, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &out_sol, &out, &err,
-                        &ticks};
-        e = coop_launch(k_trsv<T, false>, n, args, s);
-        if (e != hipSuccess) return e;
-    }
+    e = substitute<T, false>(G, 0, r, nullptr, work, z, err, s);
+    if (e != hipSuccess) return e;
     k_gather_slots<T><<<fill_grid(n), BLOCK, 0, s>>>(n, F->slot_node, z, work);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-        const int64_t* ptr = F->fptr;
-        const int32_t* col = F->fcol;
-        const T* val = (const T*)F->fval;
-        const T* dslot = (const T*)F->dslot;
-        const int32_t* slot_node = F->slot_node;
-        const double* rhs = nullptr;
-        const T* w = work;
-        T* out_sol = sol;
-        double* out = z;
-        void* args[] = {&n, &h, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &out_sol, &out, &err,
-                        &ticks};
-        e = coop_launch(k_trsv<T, true>, n, args, s);
-    }
-    return e;
+    return substitute<T, true>(F, 0, nullptr, work, sol, z, err, s);
 }
 
 // work: 2 n doubles of scratch; err: one int (0 on entry).
