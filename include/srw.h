@@ -124,7 +124,10 @@ typedef struct {
                                   level by level, get the explicit inverse of their
                                   diagonal block of Y (computed once by the build,
                                   2 x h(h+1)/2 values) and are solved by two dense
-                                  products; the other rows are substituted as before.
+                                  products; the other rows are substituted as before
+                                  (of large matrices in random order the next 131,072
+                                  rows by blocks, with the blocks' sparse inverses;
+                                  not with -1).
                                   0 (default) = min(n, 4096); -1 = none; 1..16384 =
                                   min(n, that), lowered in steps of 64 rows where a
                                   workgroup's LDS cannot hold one column of the
@@ -333,7 +336,7 @@ int srw_apply(const srw_factor* F, const double* r, double* z, void* stream);
 /* srw_apply for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and
  * the same result bit for bit, with the triangular solves' work vectors and failure
- * flag in a static scratch array of the library (one per device, 32 MiB + 256 B, held
+ * flag in a static scratch array of the library (one per device, 34 MiB + 256 B, held
  * until the process ends) instead of stream-ordered allocations.  It calls no
  * allocating routine.  Limit: F's rows <= SRW_NOALLOC_MAX_N, else SRW_E_ARG (see
  * srw_last_error).  Every call on a device shares that device's scratch: calls that

@@ -977,10 +977,10 @@ __global__ void k_gather_slots(int64_t n, const int32_t* __restrict__ slot_node,
     if (s < n) dst[s] = src[slot_node[s]];
 }
 
-// Rows past the head that hold most of the dependency chain of a random ordering: at 128^3
-// the first 8 % of the slots hold 90 % of the longest path.  One application there with
-// 32k, 64k, 128k, 192k, 256k and 400k rows: 4.20, 3.69, 3.36, 3.19, 3.10 and 2.98 ms (all
-// rows in one launch: 3.60); 2D grids and small ones have shorter chains.
+// Rows past the head that hold most of the dependency chain of a random ordering, where
+// they have no plan.  128^3, one application with 32k, 64k, 128k, 192k, 256k and 400k rows
+// in a launch of their own: 4.20, 3.69, 3.36, 3.19, 3.10 and 2.98 ms; 2D grid of 490,000:
+// 64k 626 us, 128k 668, 400k 850.
 int64_t chain_rows(int64_t n) { return std::max<int64_t>(65536, n / 8); }
 // Fewer rows than this past them are not worth a launch of their own.
 constexpr int64_t WIDE_MIN_ROWS = 65536;
@@ -2148,12 +2148,18 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             CHECK_HIP(hipGetLastError());
         }
         F->chain_end = n;
-        if (opt.solve_order != 1 && opt.ordering == SRW_ORDER_RANDOM &&
-            n - (head + chain_rows(n)) >= WIDE_MIN_ROWS)
-            F->chain_end = head + chain_rows(n);
+        F->head = head;
+        if (opt.solve_order != 1 && !batch && !ic0 && opt.head_rows >= 0 &&
+            (opt.ordering == SRW_ORDER_RANDOM || (asym && opt.ordering == SRW_ORDER_GIVEN))) {
+            if (n - head >= CHAIN_PLAN_ROWS) {
+                status = chain_build(F, head, CHAIN_PLAN_ROWS, keep, pinned, s);
+                if (status) goto done;
+            }
+            const int64_t m = F->chain.m > 0 ? F->chain.m : chain_rows(n);
+            if (F->chain.m > 0 || n - (head + m) >= WIDE_MIN_ROWS) F->chain_end = head + m;
+        }
         if (head > 0) {
             const size_t hb = (size_t)(head * (head + 1) / 2) * vbytes;
-            F->head = head;
             F->hx = ALLOC(keep, char, hb);
             F->hxt = ALLOC(keep, char, hb);
             int* herr = ALLOC(tmp, int, 1);

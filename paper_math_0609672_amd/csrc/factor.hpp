@@ -9,6 +9,19 @@
 // stored by rows (CSR, ascending node id per row, strictly lower in rank).  The
 // triangular solves run over a solve plan: the rows of Y and of Y^T listed by slot --
 // the position of a row in the order the solves take -- with columns given as slots.
+// The first rows past the head as a longer triangular system of fewer levels (chain.hip):
+// 2 m rows in the order they are substituted, for either direction.  A row's place (pos) is
+// its slot, or n + its chain row for the c of a block; columns are places.
+struct ChainPlan {
+    int64_t h = 0;  // first chain slot
+    int64_t m = 0;  // chain slots (0: no plan)
+    int64_t *fptr = nullptr, *bptr = nullptr;    // [2 m + 1]
+    int32_t *fpos = nullptr, *bpos = nullptr;    // [2 m]
+    int32_t *fnode = nullptr, *bnode = nullptr;  // [2 m] node of the row's slot
+    int32_t *fcol = nullptr, *bcol = nullptr;
+    void *fval = nullptr, *bval = nullptr;
+};
+
 struct srw_factor {
     int64_t n = 0;
     int64_t nnz_a = 0;
@@ -50,6 +63,7 @@ struct srw_factor {
     // the slots before this one hold most of the solves' dependency chain and are
     // substituted by a launch of their own (n: one launch for all)
     int64_t chain_end = 0;
+    ChainPlan chain;
     void* hx = nullptr;
     void* hxt = nullptr;
 
@@ -103,6 +117,13 @@ namespace srw {
 
 // rows of the triangular solves' dense head when srw_options.head_rows is 0
 constexpr int64_t HEAD_DEFAULT = 4096;
+// Chain rows of the chain plan, and the fewest rows past the head that it is tried for.  One
+// application with a plan of 64k, 128k, 200k and 256k rows, in us: 128^3 2,360, 2,178, 2,144,
+// 2,170; 64^3 (258,048 rows past the head) 806, 756, 842; geometric graph of 2M nodes 128k
+// 6,095, 250k 5,872.  The build pays 2 ms at 128k rows, 2.7 at 256k.  Smaller matrices gain
+// nothing (Laplace grid 50^3: 462 us an application either way) or their blocks' inverses
+// fill up (3D grid 32^3, geometric graph of 30,000 nodes).
+constexpr int64_t CHAIN_PLAN_ROWS = 131072;
 // bound on head rows x head entries (the inverse's work grows with it): about six
 // times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.6 ms)
 constexpr int64_t HEAD_COST = (int64_t)8 << 30;
@@ -213,6 +234,19 @@ int dag_depth(srw_factor* F, int32_t* depth_out, hipStream_t s);
 // columns must precede it in that order
 int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
                const int32_t* order = nullptr);
+// The levels of the rows order[0..m) (all m in order when NULL) of a CSR matrix whose
+// columns are rows that precede theirs in that list; *depth_out = the largest level + 1.
+int row_levels(int64_t m, const int32_t* order, const int64_t* ptr, const int32_t* col, int32_t* lev,
+               int32_t* depth_out, hipStream_t s);
+// The chain plan of F's slots h .. h + m - 1 (the solve plan built, in rank order); none
+// (F->chain.m = 0) where the inverses of its blocks would not stay small.
+int chain_build(srw_factor* F, int64_t h, int64_t m, Arena& keep, int64_t* pinned, hipStream_t s);
+// Scratch of one application: two vectors of the rows and of the chain's c.
+inline int64_t apply_values(const srw_factor* F)
+{
+    const int64_t m = F->chain.m, t = F->tgame ? F->tgame->chain.m : 0;
+    return 2 * (F->n + (m > t ? m : t));
+}
 void free_factor(srw_factor* F);
 int ordering_impl(int64_t n, uint64_t seed, int32_t* rank, hipStream_t s);
 int build_batched_impl(int32_t nmat, const srw_csr* A, int32_t walks_per_row, double drop_tol,

@@ -305,11 +305,12 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
     const int rg = (int)std::max<int64_t>(1, std::min<int64_t>((n + BLOCK - 1) / BLOCK, RED));
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
     double* ws = nullptr;
-    // r, rt, p, v, ph, s, sh, t, 2 n of preconditioner scratch, partials, sums, err
-    SRW_HIP(dev_alloc((void**)&ws, (10 * vec + 2 * RED + 4) * sizeof(double)));
+    // r, rt, p, v, ph, s, sh, t, preconditioner scratch, partials, sums, err
+    const size_t scratch_len = std::max<size_t>(1, F ? (size_t)apply_values(F) : 0);
+    SRW_HIP(dev_alloc((void**)&ws, (8 * vec + scratch_len + 2 * RED + 4) * sizeof(double)));
     double *r = ws, *rt = ws + vec, *p = ws + 2 * vec, *v = ws + 3 * vec, *ph = ws + 4 * vec;
     double *sv = ws + 5 * vec, *sh = ws + 6 * vec, *t = ws + 7 * vec, *work = ws + 8 * vec;
-    double* part = ws + 10 * vec;
+    double* part = work + scratch_len;
     double* sums = part + 2 * RED;
     int* err = (int*)(sums + 2);
     double* host = nullptr;

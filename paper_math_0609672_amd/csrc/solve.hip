@@ -330,8 +330,11 @@ __device__ __forceinline__ V group_reduce(V x, F f)
 // 8,150; 64^3 1,211 and 1,062; 2D grid of 490,000 674 and 626.
 constexpr int ROW_U = 2;
 
-template <typename T, bool FWD, int LPR>
-__global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
+// PLAN: rows 0..hi-1 of the chain plan, taken in their order; pos is a row's place, below n
+// for a row of X (no right-hand side), n + (chain row) for a c, h the first chain slot.
+template <typename T, bool FWD, int LPR, bool PLAN>
+__global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t n, int64_t h,
+                                                const int32_t* __restrict__ pos,
                                                 const int64_t* __restrict__ ptr,
                                                 const int32_t* __restrict__ col,
                                                 const T* __restrict__ val,
@@ -353,23 +356,31 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
     const int64_t m = hi - lo;  // rows substituted
     if (wid * G >= m) return;  // whole wave
     const int64_t step = nw * G;
-    auto slot = [&](int64_t i) { return FWD ? lo + i : hi - 1 - i; };
+    auto slot = [&](int64_t i) { return FWD || PLAN ? lo + i : hi - 1 - i; };
+    // what the row at place p (of node v) is made of, but for other rows' values
+    auto w_of = [&](int64_t p, int32_t v) -> T {
+        if (PLAN && p < n) return T(0);
+        return FWD ? w[PLAN ? p - n + h : p] : (T)rhs[v];
+    };
+    auto d_of = [&](int64_t p) -> T { return FWD && !(PLAN && p < n) ? dslot[PLAN ? p - n + h : p] : T(1); };
     // row i (this one), i + step (b: bounds and node known) and i + 2 step (a)
     int64_t i = wid * G + grp;
     int64_t q0 = 0, q1 = 0, bq0 = 0, bq1 = 0;
-    int32_t node = 0, bnode = 0;
+    int32_t node = 0, bnode = 0, at = 0, bat = 0;
     int32_t c[ROW_U];
     T v[ROW_U], base = T(0);
     if (i < m) {
         q0 = ptr[slot(i)];
         q1 = ptr[slot(i) + 1];
         node = slot_node[slot(i)];
-        base = FWD ? w[slot(i)] / dslot[slot(i)] : (T)rhs[node];
+        at = PLAN ? pos[slot(i)] : (int32_t)slot(i);
+        base = FWD ? w_of(at, node) / d_of(at) : w_of(at, node);
     }
     if (i + step < m) {
         bq0 = ptr[slot(i + step)];
         bq1 = ptr[slot(i + step) + 1];
         bnode = slot_node[slot(i + step)];
+        bat = PLAN ? pos[slot(i + step)] : (int32_t)slot(i + step);
     }
 #pragma unroll
     for (int k = 0; k < ROW_U; ++k) {
@@ -389,7 +400,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
         int32_t nc[ROW_U];
         T nv[ROW_U];
         int64_t aq0 = 0, aq1 = 0;
-        int32_t anode = 0;
+        int32_t anode = 0, aat = 0;
 #pragma unroll
         for (int k = 0; k < ROW_U; ++k) {
             const int64_t q = bq0 + k * LPR + gl;
@@ -398,17 +409,14 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
         }
         T nw_ = T(0), nd = T(1);
         if (i + step < m) {
-            if (FWD) {
-                nw_ = w[slot(i + step)];
-                nd = dslot[slot(i + step)];
-            } else {
-                nw_ = (T)rhs[bnode];
-            }
+            nw_ = w_of(bat, bnode);
+            nd = d_of(bat);
         }
         if (i + 2 * step < m) {
             aq0 = ptr[slot(i + 2 * step)];
             aq1 = ptr[slot(i + 2 * step) + 1];
             anode = slot_node[slot(i + 2 * step)];
+            aat = PLAN ? pos[slot(i + 2 * step)] : (int32_t)slot(i + 2 * step);
         }
         bool done = i >= m;
         int64_t qn = q0 + ROW_U * LPR;  // the row's entries past those in registers
@@ -453,9 +461,9 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
                 if (fin) {
                     if (gl == 0) {
                         const T x = base - sum;
-                        __hip_atomic_store((U*)sol + slot(i), __builtin_bit_cast(U, x), __ATOMIC_RELAXED,
+                        __hip_atomic_store((U*)sol + at, __builtin_bit_cast(U, x), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
-                        if (out) out[node] = (double)x;
+                        if (out && (!PLAN || at < n)) out[node] = (double)x;
                     }
                     done = true;
                 }
@@ -500,6 +508,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
         q0 = bq0;
         q1 = bq1;
         node = bnode;
+        at = bat;
         base = FWD ? nw_ / nd : nw_;
 #pragma unroll
         for (int k = 0; k < ROW_U; ++k) {
@@ -509,6 +518,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi,
         bq0 = aq0;
         bq1 = aq1;
         bnode = anode;
+        bat = aat;
     }
 }
 
@@ -715,9 +725,10 @@ __global__ __launch_bounds__(BLOCK) void k_head_mv(int64_t h, const T* __restric
     }
 }
 
-// Workgroups per CU of the chain's launch: the rows there wait for one another, and fewer
-// waves poll less.  128^3, one application: 2 to a CU 2,870 us, 4 to a CU 2,923, all that
-// fit 3,100; geometric graph of 2M nodes: 8,141, 8,537, 8,650.
+// Workgroups per CU of the launch over the chain rows: a wave per row (the row's own latency
+// counts), and few waves, whose polls slow the values they wait for.  One application with
+// the chain plan, 128^3 / 64^3 / geometric graph of 2M nodes, in us: 2 to a CU 2,173 / 809 /
+// 5,876, 4 to a CU 2,179 / 826 / 6,351; 32 lanes to a row 2,306 / 897 / 5,920.
 constexpr int CHAIN_BLOCKS_PER_CU = 2;
 
 // Grid of a cooperative launch: every block resident at once (occupancy x CUs), at most
@@ -739,57 +750,62 @@ hipError_t coop_launch(K kernel, int64_t rows, void** args, hipStream_t s, int p
                                       args, 0, s);
 }
 
-// Lanes per row of the wide part, by the factor's mean row length (a lane takes two
-// entries at once): 16 lanes up to 28 entries, 32 up to 56, a wave past them.
+// Lanes per row past the chain, by the factor's mean row length (a lane takes two entries
+// at once): 16 lanes up to 28 entries, 32 up to 56, a wave past them.
 template <typename T, bool FWD>
-hipError_t trsv_launch(const srw_factor* F, int64_t rows, bool chain, void** args, hipStream_t s)
+hipError_t trsv_launch(const srw_factor* F, int64_t rows, void** args, hipStream_t s)
 {
-    if (chain)  // a wave per row: the row's own latency counts
-        return coop_launch(k_trsv<T, FWD, 64>, rows, args, s, F->chain_end < F->n ? CHAIN_BLOCKS_PER_CU : 64);
-    if (F->nnz_y > 56 * F->n) return coop_launch(k_trsv<T, FWD, 64>, rows, args, s);
-    if (F->nnz_y > 28 * F->n) return coop_launch(k_trsv<T, FWD, 32>, (rows + 1) / 2, args, s);
-    return coop_launch(k_trsv<T, FWD, 16>, (rows + 3) / 4, args, s);
+    if (F->nnz_y > 56 * F->n) return coop_launch(k_trsv<T, FWD, 64, false>, rows, args, s);
+    if (F->nnz_y > 28 * F->n) return coop_launch(k_trsv<T, FWD, 32, false>, (rows + 1) / 2, args, s);
+    return coop_launch(k_trsv<T, FWD, 16, false>, (rows + 3) / 4, args, s);
 }
 
 int fill_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(grid_for(n, BLOCK), 1), 2048); }
 
 // The substitution over slots h..n-1 of one triangle of the plan, in two launches: the
-// slots before chain_end hold most of the dependency chain and little work, the others
-// the work.
+// slots before chain_end hold most of the dependency chain, the others most of the work.
 template <typename T, bool FWD>
 hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T* w, T* sol, double* out,
                       int* err, hipStream_t s)
 {
-    const int64_t n = F->n;
-    const int64_t* ptr = FWD ? F->fptr : F->bptr;
-    const int32_t* col = FWD ? F->fcol : F->bcol;
-    const T* val = (const T*)(FWD ? F->fval : F->bval);
+    int64_t n = F->n;
+    const ChainPlan& C = F->chain;
     const T* dslot = FWD ? (const T*)F->dslot : nullptr;
-    const int32_t* slot_node = F->slot_node;
     int64_t ticks = wait_ticks(5.0);
     for (int part = 0; part < 2; ++part) {
-        const bool chain = (part == 0) == FWD;
-        int64_t lo = chain ? h : F->chain_end, hi = chain ? F->chain_end : n;
+        const bool chain = (part == 0) == FWD, plan = chain && C.m > 0;
+        int64_t lo = plan ? 0 : chain ? h : F->chain_end, hi = plan ? 2 * C.m : chain ? F->chain_end : n;
         if (lo >= hi) continue;
-        void* args[] = {&lo, &hi, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &sol, &out, &err, &ticks};
-        const hipError_t e = trsv_launch<T, FWD>(F, hi - lo, chain, args, s);
+        const int64_t* ptr = plan ? (FWD ? C.fptr : C.bptr) : FWD ? F->fptr : F->bptr;
+        const int32_t* col = plan ? (FWD ? C.fcol : C.bcol) : FWD ? F->fcol : F->bcol;
+        const T* val = (const T*)(plan ? (FWD ? C.fval : C.bval) : FWD ? F->fval : F->bval);
+        const int32_t* slot_node = plan ? (FWD ? C.fnode : C.bnode) : F->slot_node;
+        const int32_t* pos = plan ? (FWD ? C.fpos : C.bpos) : nullptr;
+        void* args[] = {&lo, &hi, &n, &h, &pos, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &sol, &out, &err, &ticks};
+        hipError_t e;
+        if (plan)
+            e = coop_launch(k_trsv<T, FWD, 64, true>, hi, args, s, CHAIN_BLOCKS_PER_CU);
+        else if (chain)
+            e = coop_launch(k_trsv<T, FWD, 64, false>, hi - lo, args, s, F->chain_end < n ? CHAIN_BLOCKS_PER_CU : 64);
+        else
+            e = trsv_launch<T, FWD>(F, hi - lo, args, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// work, sol: n values of T each; z (node order) receives the result as doubles.
+// work: apply_values(F) values of T; z (node order) receives the result as doubles.
 template <typename T>
-hipError_t apply_plan(const srw_factor* F, const double* r, T* work, T* sol, double* z, int* err,
+hipError_t apply_plan(const srw_factor* F, const double* r, T* work, double* z, int* err,
                       hipStream_t s)
 {
     const int64_t n = F->n;
     const int64_t h = F->head;
+    T* sol = work + apply_values(F) / 2;
     hipError_t e = hipSuccess;
     const unsigned hg = (unsigned)((h + BLOCK / 64 - 1) / (BLOCK / 64));
     if (n > h) {
-        k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, work);
-        k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, sol);
+        k_fill_sentinel<T><<<fill_grid(apply_values(F)), BLOCK, 0, s>>>(apply_values(F), work);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         e = substitute<T, false>(F, h, r, nullptr, work, nullptr, err, s);
         if (e != hipSuccess) return e;
@@ -820,13 +836,13 @@ __global__ void k_gather_slots(int64_t n, const int32_t* __restrict__ slot_node,
 }
 
 template <typename T>
-hipError_t apply_ldu_plan(const srw_factor* F, const double* r, T* work, T* sol, double* z,
-                          int* err, hipStream_t s)
+hipError_t apply_ldu_plan(const srw_factor* F, const double* r, T* work, double* z, int* err,
+                          hipStream_t s)
 {
     const srw_factor* G = F->tgame;
     const int64_t n = F->n;  // (the games' factors take no dense head)
-    k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, work);
-    k_fill_sentinel<T><<<fill_grid(n), BLOCK, 0, s>>>(n, sol);
+    T* sol = work + apply_values(F) / 2;
+    k_fill_sentinel<T><<<fill_grid(apply_values(F)), BLOCK, 0, s>>>(apply_values(F), work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = substitute<T, false>(G, 0, r, nullptr, work, z, err, s);
@@ -836,25 +852,16 @@ hipError_t apply_ldu_plan(const srw_factor* F, const double* r, T* work, T* sol,
     return substitute<T, true>(F, 0, nullptr, work, sol, z, err, s);
 }
 
-// work: 2 n doubles of scratch; err: one int (0 on entry).
+// work: apply_values(F) doubles of scratch; err: one int (0 on entry).
 hipError_t apply_any(const srw_factor* F, const double* r, void* work, double* z, int* err,
                      hipStream_t s)
 {
     if (F->n == 0) return hipSuccess;
-    if (F->tgame) {
-        if (F->precision == SRW_FP32) {
-            float* w = (float*)work;
-            return apply_ldu_plan<float>(F, r, w, w + F->n, z, err, s);
-        }
-        double* w = (double*)work;
-        return apply_ldu_plan<double>(F, r, w, w + F->n, z, err, s);
-    }
-    if (F->precision == SRW_FP32) {
-        float* w = (float*)work;
-        return apply_plan<float>(F, r, w, w + F->n, z, err, s);
-    }
-    double* w = (double*)work;
-    return apply_plan<double>(F, r, w, w + F->n, z, err, s);
+    if (F->tgame)
+        return F->precision == SRW_FP32 ? apply_ldu_plan<float>(F, r, (float*)work, z, err, s)
+                                        : apply_ldu_plan<double>(F, r, (double*)work, z, err, s);
+    return F->precision == SRW_FP32 ? apply_plan<float>(F, r, (float*)work, z, err, s)
+                                    : apply_plan<double>(F, r, (double*)work, z, err, s);
 }
 
 int red_grid(int64_t n)
@@ -941,11 +948,10 @@ hipError_t apply_factor(const srw_factor* F, const double* r, void* work, double
 
 int apply_impl(srw_factor* F, const double* r, double* z, hipStream_t s)
 {
-    const int64_t n = F->n;
     char* ws = nullptr;
-    const size_t vec = (size_t)std::max<int64_t>(n, 1);
-    SRW_HIP(dev_alloc((void**)&ws, 2 * vec * sizeof(double) + 64));
-    int* err = (int*)(ws + 2 * vec * sizeof(double));
+    const size_t vec = (size_t)std::max<int64_t>(apply_values(F), 1);
+    SRW_HIP(dev_alloc((void**)&ws, vec * sizeof(double) + 64));
+    int* err = (int*)(ws + vec * sizeof(double));
     hipError_t e = hipMemsetAsync(err, 0, sizeof(int), s);
     if (e == hipSuccess) e = apply_any(F, r, ws, z, err, s);
     int herr = 0;
@@ -959,9 +965,11 @@ int apply_impl(srw_factor* F, const double* r, double* z, hipStream_t s)
 
 // ------------------------------------------------------ allocation-free application
 // Scratch of srw_apply_noalloc: the two work vectors of the triangular solves (up to
-// SRW_NOALLOC_MAX_N values each, FP64 or FP32) and the solves' failure flag.  One copy
+// SRW_NOALLOC_MAX_N rows and their chain rows each, FP64 or FP32) and the solves' failure
+// flag.  One copy
 // per device, held until the process ends; every call on a device shares it.
-constexpr size_t NOALLOC_WORK_BYTES = 2 * (size_t)SRW_NOALLOC_MAX_N * sizeof(double);
+constexpr size_t NOALLOC_WORK_BYTES =
+    2 * ((size_t)SRW_NOALLOC_MAX_N + (size_t)CHAIN_PLAN_ROWS) * sizeof(double);
 static __device__ __align__(256) unsigned char scratch[NOALLOC_WORK_BYTES + 256];
 
 namespace {
@@ -1016,27 +1024,24 @@ int apply_noalloc_impl(const srw_factor* F, const double* r, double* z, hipStrea
     return SRW_OK;
 }
 
-int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
-               const int32_t* order)
+int row_levels(int64_t m, const int32_t* order, const int64_t* ptr, const int32_t* col, int32_t* lev,
+               int32_t* depth_out, hipStream_t s)
 {
-    int64_t n = F->n;
     *depth_out = 0;
-    if (n == 0) return SRW_OK;
+    if (m == 0) return SRW_OK;
     char* ws = nullptr;
     SRW_HIP(dev_alloc((void**)&ws, 64));
     int* depth = (int*)ws;
     int* err = depth + 1;
     hipError_t e = hipMemsetAsync(depth, 0, 2 * sizeof(int), s);
     if (e == hipSuccess) {
-        k_fill_sentinel<int32_t><<<fill_grid(n), BLOCK, 0, s>>>(n, lev);
+        k_fill_sentinel<int32_t><<<fill_grid(m), BLOCK, 0, s>>>(m, lev);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        const int64_t* ptr = F->fptr;
-        const int32_t* col = F->fcol;
         int64_t ticks = wait_ticks(5.0);
-        void* args[] = {&n, &order, &ptr, &col, &lev, &depth, &err, &ticks};
-        e = coop_launch(k_levels, n, args, s);
+        void* args[] = {&m, &order, &ptr, &col, &lev, &depth, &err, &ticks};
+        e = coop_launch(k_levels, m, args, s);
     }
     int host[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(host, depth, 2 * sizeof(int), hipMemcpyDeviceToHost, s);
@@ -1047,6 +1052,12 @@ int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
     if (host[1]) return SRW_E_HIP;
     *depth_out = host[0];
     return SRW_OK;
+}
+
+int dag_levels(srw_factor* F, int32_t* lev, int32_t* depth_out, hipStream_t s,
+               const int32_t* order)
+{
+    return row_levels(F->n, order, F->fptr, F->fcol, lev, depth_out, s);
 }
 
 int dag_depth(srw_factor* F, int32_t* depth_out, hipStream_t s)
@@ -1071,9 +1082,10 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
     double* ws = nullptr;
     double* host = nullptr;
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
-    SRW_HIP(dev_alloc((void**)&ws, (6 * vec + RED_GRID + S_COUNT + 4) * sizeof(double)));
+    const size_t scratch_len = std::max<size_t>(1, F ? (size_t)apply_values(F) : 0);
+    SRW_HIP(dev_alloc((void**)&ws, (4 * vec + scratch_len + RED_GRID + S_COUNT + 4) * sizeof(double)));
     double *r = ws, *z = ws + vec, *p = ws + 2 * vec, *q = ws + 3 * vec, *work = ws + 4 * vec;
-    double* partials = ws + 6 * vec;
+    double* partials = work + scratch_len;
     double* sc = partials + RED_GRID;
     int* err = (int*)(sc + S_COUNT);
     host = host_scratch() ? (double*)(host_scratch() + 8) : nullptr;

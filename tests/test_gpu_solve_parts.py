@@ -1,6 +1,7 @@
 """The triangular solves past the dense head in two launches (a wave per row over the chain,
 16, 32 or 64 lanes per row over the rest, by the factor's mean row length), against the oracle,
-and at the smallest size that takes two launches."""
+at the smallest size that takes two launches, and where the chain rows are solved by blocks
+with the blocks' inverses: 131,072 rows or more past the head, blocks deep enough."""
 import numpy as np
 import pytest
 
@@ -38,3 +39,49 @@ def test_apply_matches_oracle(srw, name):  # noqa: F811
             got = np_(srw.apply(F, torch.as_tensor(r, device=DEV)))
             assert np.linalg.norm(got - z) <= tol * np.linalg.norm(z), precision
         F.free()
+
+
+# the chain plan over the last row, on matrices of no geometry (whose blocks have to be made
+# smaller with longer rows), and on long chains (few grounded nodes)
+PLANS = {
+    "plan_takes_all_rows": (W.grid((48, 64, 44), ground_frac=0.02, seed=3), 256, 1e-4),
+    "random_graph": (W.random_graph(140000, 420000, seed=7, ground_frac=0.01), 64, 1e-3),
+    "smaller_blocks": (W.random_graph(140000, 1120000, seed=7, ground_frac=0.01), 64, 1e-3),
+    "long_chains": (W.grid((53, 51, 52), ground_frac=0.0005, seed=3), 256, 1e-4),
+}
+
+
+@pytest.mark.parametrize("name", list(PLANS))
+def test_chain_plan_matches_oracle(srw, name):  # noqa: F811
+    """The bound of every apply test (1e-12, 1e-5 with the FP32 factor); the application
+    without allocations and a second factor of the same seed give the same bits."""
+    A, walks, drop = PLANS[name]
+    ref = O.build_factor(A, walks, drop, 7, threads=8)
+    M = srw.Matrix.from_host(A, DEV)
+    r = W.rhs(A.n, seed=5)
+    rt = torch.as_tensor(r, device=DEV)
+    z = O.apply(ref, r)
+    for precision, tol in (("fp64", 1e-12), ("fp32", 1e-5)):
+        F = srw.build_factor(M, walks, drop, 7, precision=precision)
+        G = srw.build_factor(M, walks, drop, 7, precision=precision)
+        got = np_(srw.apply(F, rt))
+        assert np.linalg.norm(got - z) <= tol * np.linalg.norm(z), precision
+        assert np.array_equal(np_(srw.apply_noalloc(F, rt)), got)
+        assert np.array_equal(np_(srw.apply(G, rt)), got)
+        F.free()
+        G.free()
+
+
+def test_chain_plan_of_two_games(srw):  # noqa: F811
+    """The plans of the two games' factors (no dense head), preconditioning BiCGSTAB: the
+    oracle's first iterates to 1e-10, as in the tests of smaller sizes."""
+    A = W.grid_asym((53, 51, 52), ground_frac=0.0005, seed=3)
+    ref = O.build_factor_ldu(A, 64, 1e-3, 7)
+    M = srw.Matrix.from_host(A, DEV)
+    F = srw.build_factor_ldu(M, 64, 1e-3, 7)
+    b = W.rhs(A.n, seed=5)
+    for k in (1, 2):
+        _, x, _, _ = srw.bicgstab_solve(M, F, torch.as_tensor(b, device=DEV), 0.0, k)
+        _, rx, _, _ = O.bicgstab(A, ref, b, 0.0, k)
+        assert np.linalg.norm(np_(x) - rx) <= 1e-10 * np.linalg.norm(rx)
+    F.free()
