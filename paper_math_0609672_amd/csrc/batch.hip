@@ -166,6 +166,11 @@ __global__ __launch_bounds__(BLOCK) void k_tile(Tiles tl, int nrhs, const int64_
     const int64_t t = blockIdx.x;
     const int32_t m = tl.mat[t];
     const int64_t r0 = tl.row0[t], r1 = tl.row0[t + 1];
+    if (OP == T_PQ || OP == T_UPD || OP == T_DOT) {  // sums that no stopped system reads
+        bool any = false;
+        for (int j = 0; j < nrhs; ++j) any = any || sys[(int64_t)m * nrhs + j].active;
+        if (!any) return;
+    }
     double acc[MAXR];
 #pragma unroll
     for (int j = 0; j < MAXR; ++j) acc[j] = 0.0;
@@ -180,9 +185,25 @@ __global__ __launch_bounds__(BLOCK) void k_tile(Tiles tl, int nrhs, const int64_
         if (OP == T_PQ || OP == T_RES) {
             const int64_t i = r0 + fr / nrhs;
             const double* src = OP == T_PQ ? u : v;  // p, or x
+            // four entries at once: their columns, then their values of src, are in
+            // flight together (one at a time: 1,010 us on 10M rows of 8 right-hand sides,
+            // 750 us this way)
             double sum = 0.0;
-            for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e)
-                sum += val[e] * src[(int64_t)col[e] * nrhs + j];
+            const int64_t e1 = rowptr[i + 1];
+            for (int64_t e = rowptr[i]; e < e1; e += 4) {
+                int32_t c[4];
+                double a[4], x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    c[k] = e + k < e1 ? col[e + k] : -1;
+                    a[k] = e + k < e1 ? val[e + k] : 0.0;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = c[k] >= 0 ? src[(int64_t)c[k] * nrhs + j] : 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (c[k] >= 0) sum += a[k] * x[k];
+            }
             if (OP == T_PQ) {
                 w[f] = sum;
                 add = u[f] * sum;
@@ -221,12 +242,17 @@ __global__ void k_bfinal(int64_t nsys, int nrhs, const int64_t* __restrict__ mat
                          const double* __restrict__ partials, Sys* __restrict__ sys, int op,
                          double tol, int32_t max_iter, int* __restrict__ active_count)
 {
-    const int64_t sidx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // sixteen lanes per system, their sums added by a butterfly (one thread per system was
+    // one chain of loads: 74 us on 40 tiles, 7 us this way)
+    const int64_t sidx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 16;
     if (sidx >= nsys) return;
     const int64_t m = sidx / nrhs;
     const int j = (int)(sidx % nrhs);
     double s = 0.0;
-    for (int64_t t = mat_tile[m]; t < mat_tile[m + 1]; ++t) s += partials[t * nrhs + j];
+    for (int64_t t = mat_tile[m] + threadIdx.x % 16; t < mat_tile[m + 1]; t += 16) s += partials[t * nrhs + j];
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x % 16 != 0) return;
     Sys& S = sys[sidx];
     switch (op) {
         case B_BB:
@@ -532,6 +558,9 @@ __device__ __forceinline__ void load_row8(const float* p, float (&x)[MAXR])
 // entries and partial sums go exactly as in k_trsv_multi (lane j: entries j, j + RG,
 // ..., a zero product where a round runs past the row; then the butterfly), so both
 // kernels give the same bits.  Lane j of a row writes right-hand side j.
+// Large levels run near the rate of memory (320,000 rows: 3.4 TB/s); the levels of a few
+// thousand long rows are chains of loads, so a row's rounds go two at once (256 pruned
+// grids, 8 right-hand sides, mean level: 21.3 -> 19.8 us backward, 18.2 -> 16.4 forward).
 template <typename T, bool FWD>
 __global__ __launch_bounds__(BLOCK) void k_trsv_level(int64_t a, int64_t b, int nrhs,
                                                       const int64_t* __restrict__ ptr,
@@ -541,7 +570,8 @@ __global__ __launch_bounds__(BLOCK) void k_trsv_level(int64_t a, int64_t b, int 
                                                       const int32_t* __restrict__ slot_node,
                                                       const double* __restrict__ rhs,
                                                       const T* __restrict__ w, T* __restrict__ sol,
-                                                      double* __restrict__ out)
+                                                      double* __restrict__ out,
+                                                      const int* __restrict__ active)
 {
     const int64_t s = a + ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / RG;
     const int j = (int)(threadIdx.x % RG);
@@ -551,23 +581,49 @@ __global__ __launch_bounds__(BLOCK) void k_trsv_level(int64_t a, int64_t b, int 
     for (int jr = 0; jr < MAXR; ++jr) acc[jr] = T(0);
     if (row) {
         const int64_t q0 = ptr[s], q1 = ptr[s + 1];
-        for (int64_t qb = q0; qb < q1; qb += RG) {
-            const int64_t q = qb + j;
-            const bool ok = q < q1;
-            const int32_t c = ok ? col[q] : 0;
-            const T av = ok ? val[q] : T(0);
-            const T* src = sol + (int64_t)c * nrhs;
-            T xv[MAXR];
-            if (nrhs == MAXR) {
-                load_row8(src, xv);  // a whole row of values in 16-byte loads
-            } else {
+        // two rounds at once, the columns of the next two loaded meanwhile
+        int32_t c[2];
+        T av[2];
 #pragma unroll
-                for (int jr = 0; jr < MAXR; ++jr) xv[jr] = jr < nrhs ? src[jr] : T(0);
+        for (int u = 0; u < 2; ++u) {
+            const int64_t q = q0 + u * RG + j;
+            c[u] = q < q1 ? col[q] : -1;
+            av[u] = q < q1 ? val[q] : T(0);
+        }
+        if (active && *active == 0) return;  // no system left (all blocks alike)
+        for (int64_t qb = q0; qb < q1; qb += 2 * RG) {
+            T xv[2][MAXR];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const T* src = sol + (int64_t)(c[u] < 0 ? 0 : c[u]) * nrhs;
+                if (u > 0 && qb + RG >= q1) {
+#pragma unroll
+                    for (int jr = 0; jr < MAXR; ++jr) xv[u][jr] = T(0);
+                } else if (nrhs == MAXR) {
+                    load_row8(src, xv[u]);  // a whole row of values in 16-byte loads
+                } else {
+#pragma unroll
+                    for (int jr = 0; jr < MAXR; ++jr) xv[u][jr] = jr < nrhs ? src[jr] : T(0);
+                }
+            }
+            int32_t nc[2];
+            T na[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int64_t q = qb + (2 + u) * RG + j;
+                nc[u] = q < q1 ? col[q] : -1;
+                na[u] = q < q1 ? val[q] : T(0);
             }
 #pragma unroll
-            for (int jr = 0; jr < MAXR; ++jr) {
-                const T x = ok ? xv[jr] : T(0);
-                acc[jr] += av * x;
+            for (int u = 0; u < 2; ++u) {
+                if (u > 0 && qb + RG >= q1) break;  // a round past the row adds nothing
+#pragma unroll
+                for (int jr = 0; jr < MAXR; ++jr) acc[jr] += av[u] * (c[u] < 0 ? T(0) : xv[u][jr]);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                c[u] = nc[u];
+                av[u] = na[u];
             }
         }
     }
@@ -765,7 +821,7 @@ hipError_t solve_launch(K kernel, int64_t rows, int chunk, int per_cu_cap, void*
 }
 
 template <typename T>
-hipError_t batch_apply(const srw_factor* F, BatchWork& W, const Sched& sc, hipStream_t s)
+hipError_t batch_apply(const srw_factor* F, BatchWork& W, const Sched& sc, hipStream_t s, const int* active)
 {
     int64_t n = F->n;
     int nrhs = W.nrhs;
@@ -782,14 +838,14 @@ hipError_t batch_apply(const srw_factor* F, BatchWork& W, const Sched& sc, hipSt
             if (b <= a) continue;
             k_trsv_level<T, false><<<(unsigned)((b - a + per_block - 1) / per_block), BLOCK, 0, s>>>(
                 a, b, nrhs, F->bptr, F->bcol, (const T*)F->bval, nullptr, F->slot_node, W.r,
-                nullptr, work, nullptr);
+                nullptr, work, nullptr, active);
         }
         for (int l = 0; l < L; ++l) {
             const int64_t a = lp[l], b = lp[l + 1];
             if (b <= a) continue;
             k_trsv_level<T, true><<<(unsigned)((b - a + per_block - 1) / per_block), BLOCK, 0, s>>>(
                 a, b, nrhs, F->fptr, F->fcol, (const T*)F->fval, (const T*)F->dslot, F->slot_node,
-                nullptr, work, sol, W.z);
+                nullptr, work, sol, W.z, active);
         }
         return hipGetLastError();
     }
@@ -834,9 +890,12 @@ hipError_t batch_apply(const srw_factor* F, BatchWork& W, const Sched& sc, hipSt
     return e;
 }
 
-hipError_t apply_b(const srw_factor* F, BatchWork& W, const Sched& sc, hipStream_t s)
+// active (if given): device count of the systems still iterated; nothing is done at 0.
+hipError_t apply_b(const srw_factor* F, BatchWork& W, const Sched& sc, hipStream_t s,
+                   const int* active = nullptr)
 {
-    return F->precision == SRW_FP32 ? batch_apply<float>(F, W, sc, s) : batch_apply<double>(F, W, sc, s);
+    return F->precision == SRW_FP32 ? batch_apply<float>(F, W, sc, s, active)
+                                    : batch_apply<double>(F, W, sc, s, active);
 }
 
 // z = M^{-1} r, then rho / p for the active systems (restart = 1: p = z)
@@ -845,7 +904,7 @@ hipError_t iteration(const srw_factor* F, BatchWork& W, const Sched& sc, double*
 {
     const srw_csr& A = F->Acat;
     const int nrhs = W.nrhs;
-    const int sg = (int)((W.nsys + 255) / 256);
+    const int sg = (int)((16 * W.nsys + 255) / 256);
     const int64_t nv = W.N * nrhs;
     hipError_t e;
     k_tile<T_PQ><<<(unsigned)W.ntile, BLOCK, 0, s>>>(W.tiles, nrhs, A.rowptr, A.col, A.val, W.p,
@@ -856,7 +915,7 @@ hipError_t iteration(const srw_factor* F, BatchWork& W, const Sched& sc, double*
                                                       W.q, X, W.r, W.sys, W.partials);
     k_bfinal<<<sg, 256, 0, s>>>(W.nsys, nrhs, W.mat_tile, W.partials, W.sys, B_RR, tol, max_iter, W.active);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = apply_b(F, W, sc, s)) != hipSuccess) return e;
+    if ((e = apply_b(F, W, sc, s, W.active)) != hipSuccess) return e;
     k_tile<T_DOT><<<(unsigned)W.ntile, BLOCK, 0, s>>>(W.tiles, nrhs, nullptr, nullptr, nullptr, W.r,
                                                       W.z, nullptr, nullptr, W.sys, W.partials);
     k_bfinal<<<sg, 256, 0, s>>>(W.nsys, nrhs, W.mat_tile, W.partials, W.sys, B_BETA, tol, max_iter, W.active);
@@ -1009,7 +1068,7 @@ int pcg_batched_impl(srw_factor* F, int32_t nrhs, const double* B, double tol, i
     Sched tuning{};  // schedule being timed when a solve failed (per_cu 0: not while tuning)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    const int sg = (int)((W.nsys + 255) / 256);
+    const int sg = (int)((16 * W.nsys + 255) / 256);
     const srw_csr& A = F->Acat;
     auto sync_flags = [&]() -> hipError_t {
         hipError_t ee = hipMemcpyAsync(host_flag, W.active, 8 * sizeof(int), hipMemcpyDeviceToHost, s);
