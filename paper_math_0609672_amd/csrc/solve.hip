@@ -603,14 +603,34 @@ __global__ __launch_bounds__(64 * HINV_WAVES) void k_head_inverse(int64_t h,
     __syncthreads();
     const int64_t t0 = wall_clock64();
     bool failed = false;
+    // a row's first entries are loaded a row ahead, its bounds two (Laplace grid 50^3, 4,096
+    // rows: 1,250 us without, 988 with and with sums across lanes off LDS)
+    auto bounds = [&](int64_t i, int64_t& b0, int64_t& b1) {
+        b0 = i < h ? ptr[i] : 0;
+        b1 = i < h ? ptr[i + 1] : 0;
+    };
+    int64_t q0, q1, n0, n1;
+    bounds(c0 + wv, q0, q1);
+    bounds(c0 + wv + HINV_WAVES, n0, n1);
+    int32_t fq = q0 + lane < q1 ? col[q0 + lane] : -1;
+    T fy = q0 + lane < q1 ? val[q0 + lane] : T(0);
     for (int64_t i = c0 + wv; i < h; i += HINV_WAVES) {
         T acc[W];
 #pragma unroll
         for (int k = 0; k < W; ++k) acc[k] = T(0);
-        const int64_t q1 = ptr[i + 1];
-        for (int64_t qb = ptr[i]; qb < q1; qb += 64) {
-            const bool has = qb + lane < q1;
-            const int32_t q = has ? col[qb + lane] : -1;
+        int32_t q = fq;
+        T y = fy;
+        const int64_t p0 = q0, p1 = q1;
+        q0 = n0;
+        q1 = n1;
+        fq = q0 + lane < q1 ? col[q0 + lane] : -1;
+        fy = q0 + lane < q1 ? val[q0 + lane] : T(0);
+        bounds(i + 2 * HINV_WAVES, n0, n1);
+        for (int64_t qb = p0; qb < p1; qb += 64) {
+            if (qb > p0) {
+                q = qb + lane < p1 ? col[qb + lane] : -1;
+                y = qb + lane < p1 ? val[qb + lane] : T(0);
+            }
             const bool dep = q >= c0;  // rows below c0 are zero on these columns
             const int64_t r = dep ? (int64_t)q - c0 : 0;
             uint32_t spins = 0;
@@ -625,7 +645,6 @@ __global__ __launch_bounds__(64 * HINV_WAVES) void k_head_inverse(int64_t h,
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             if (dep) {
-                const T y = val[qb + lane];
 #pragma unroll
                 for (int k = 0; k < W; ++k) acc[k] = acc[k] + y * xv[r * W + k];
             }
@@ -634,7 +653,7 @@ __global__ __launch_bounds__(64 * HINV_WAVES) void k_head_inverse(int64_t h,
 #pragma unroll
         for (int k = 0; k < W; ++k) {
             const int64_t j = c0 + k;
-            const T sk = wave_sum(acc[k]);
+            const T sk = group_reduce<64>(acc[k], [](T p, T q) { return p + q; });
             x[k] = j > i ? T(0) : (j == i ? T(1) : T(0)) - sk;
         }
         if (lane < W) {
@@ -701,8 +720,11 @@ __global__ __launch_bounds__(BLOCK) void k_head_rhs(int64_t h, const int64_t* __
     if (lane == 0) c[i] = (T)rhs[slot_node[i]] - acc;
 }
 
-// One wave per row r of the packed matrix M: FWD, row r of X times (w / D) over the
-// head; otherwise row r of X^T times c[r..h-1].  Results to y (and by node to out).
+// One wave per row r of the packed matrix M: FWD, row r of X times v (= w / D) over the
+// head, the result by node to out; otherwise row r of X^T times c[r..h-1], divided by D for
+// the forward product.  4,096 rows are 67 MB, most of
+// it in the memory-side cache: 35 us with one load of a lane in flight (and a division per
+// product), 16 us with eight.
 template <typename T, bool FWD>
 __global__ __launch_bounds__(BLOCK) void k_head_mv(int64_t h, const T* __restrict__ M,
                                                    const T* __restrict__ v,
@@ -714,13 +736,21 @@ __global__ __launch_bounds__(BLOCK) void k_head_mv(int64_t h, const T* __restric
     const int64_t r = (int64_t)blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
     if (r >= h) return;  // whole wave
     const T* row = M + (FWD ? head_roff(r) : head_toff(r, h));
+    const T* x = FWD ? v : v + r;
     const int64_t len = FWD ? r + 1 : h - r;
     T acc = T(0);
-    for (int64_t k = lane; k < len; k += 64)
-        acc += row[k] * (FWD ? v[k] / dslot[k] : v[r + k]);
-    acc = wave_sum(acc);
+    int64_t k = lane;
+    for (; k + 7 * 64 < len; k += 8 * 64) {  // eight loads of the row in flight
+        T m[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m[u] = row[k + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += m[u] * x[k + 64 * u];
+    }
+    for (; k < len; k += 64) acc += row[k] * x[k];
+    acc = group_reduce<64>(acc, [](T p, T q) { return p + q; });
     if (lane == 0) {
-        y[r] = acc;
+        y[r] = FWD ? acc : acc / dslot[r];
         if (FWD && out) out[slot_node[r]] = (double)acc;
     }
 }
@@ -814,10 +844,9 @@ hipError_t apply_plan(const srw_factor* F, const double* r, T* work, double* z, 
         // backward head (c in sol's head slots, then w_head), forward head
         k_head_rhs<T><<<hg, BLOCK, 0, s>>>(h, F->bptr, F->bcol, (const T*)F->bval, F->slot_node, r,
                                            work, sol);
-        k_head_mv<T, false><<<hg, BLOCK, 0, s>>>(h, (const T*)F->hxt, sol, nullptr, nullptr, work,
+        k_head_mv<T, false><<<hg, BLOCK, 0, s>>>(h, (const T*)F->hxt, sol, (const T*)F->dslot, nullptr, work,
                                                  nullptr);
-        k_head_mv<T, true><<<hg, BLOCK, 0, s>>>(h, (const T*)F->hx, work, (const T*)F->dslot,
-                                                F->slot_node, sol, z);
+        k_head_mv<T, true><<<hg, BLOCK, 0, s>>>(h, (const T*)F->hx, work, nullptr, F->slot_node, sol, z);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (n > h) e = substitute<T, true>(F, h, nullptr, work, sol, z, err, s);
