@@ -982,6 +982,15 @@ __global__ void k_gather_slots(int64_t n, const int32_t* __restrict__ slot_node,
 // in a launch of their own: 4.20, 3.69, 3.36, 3.19, 3.10 and 2.98 ms; 2D grid of 490,000:
 // 64k 626 us, 128k 668, 400k 850.
 int64_t chain_rows(int64_t n) { return std::max<int64_t>(65536, n / 8); }
+// Workgroups per CU of the launch over the chain rows: a wave per row (the row's own latency
+// counts), and few waves, whose polls slow the values they wait for.  One application with
+// the chain plan, 128^3 / 64^3 / geometric graph of 2M nodes, in us: 2 to a CU 2,173 / 809 /
+// 5,876, 4 to a CU 2,179 / 826 / 6,351; 32 lanes to a row 2,306 / 897 / 5,920.  Where it
+// takes all rows past the head, Laplace 50^3 / grid 48^3 / geometric graph of 30,000 nodes /
+// 2D grid 300^2: 2 to a CU 454 / 691 / 905 / 360, 4 432 / 704 / 979 / 338, 7 449 / 752 /
+// 1,093 / 338.  (Other orderings, whose chain runs through all rows, take all that fit.)
+constexpr int32_t CHAIN_PER_CU = 2;
+constexpr int32_t ALL_PER_CU = 4;
 // Fewer rows than this past them are not worth a launch of their own.
 constexpr int64_t WIDE_MIN_ROWS = 65536;
 
@@ -2162,6 +2171,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             }
             const int64_t m = F->chain.m > 0 ? F->chain.m : chain_rows(n);
             if (F->chain.m > 0 || n - (head + m) >= WIDE_MIN_ROWS) F->chain_end = head + m;
+            F->chain_per_cu = F->chain_end < n || F->chain.m > 0 ? CHAIN_PER_CU : ALL_PER_CU;
         }
         if (head > 0) {
             const size_t hb = (size_t)(head * (head + 1) / 2) * vbytes;

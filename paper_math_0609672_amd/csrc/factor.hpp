@@ -63,6 +63,7 @@ struct srw_factor {
     // the slots before this one hold most of the solves' dependency chain and are
     // substituted by a launch of their own (n: one launch for all)
     int64_t chain_end = 0;
+    int32_t chain_per_cu = 64;  // workgroups per CU of that launch, at most
     ChainPlan chain;
     void* hx = nullptr;
     void* hxt = nullptr;

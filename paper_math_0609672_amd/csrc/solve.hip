@@ -755,12 +755,6 @@ __global__ __launch_bounds__(BLOCK) void k_head_mv(int64_t h, const T* __restric
     }
 }
 
-// Workgroups per CU of the launch over the chain rows: a wave per row (the row's own latency
-// counts), and few waves, whose polls slow the values they wait for.  One application with
-// the chain plan, 128^3 / 64^3 / geometric graph of 2M nodes, in us: 2 to a CU 2,173 / 809 /
-// 5,876, 4 to a CU 2,179 / 826 / 6,351; 32 lanes to a row 2,306 / 897 / 5,920.
-constexpr int CHAIN_BLOCKS_PER_CU = 2;
-
 // Grid of a cooperative launch: every block resident at once (occupancy x CUs), at most
 // per_cu_cap per CU, capped at the blocks the work can use (rows: one per wave).
 template <typename K>
@@ -814,9 +808,9 @@ hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T
         void* args[] = {&lo, &hi, &n, &h, &pos, &ptr, &col, &val, &dslot, &slot_node, &rhs, &w, &sol, &out, &err, &ticks};
         hipError_t e;
         if (plan)
-            e = coop_launch(k_trsv<T, FWD, 64, true>, hi, args, s, CHAIN_BLOCKS_PER_CU);
+            e = coop_launch(k_trsv<T, FWD, 64, true>, hi, args, s, F->chain_per_cu);
         else if (chain)
-            e = coop_launch(k_trsv<T, FWD, 64, false>, hi - lo, args, s, F->chain_end < n ? CHAIN_BLOCKS_PER_CU : 64);
+            e = coop_launch(k_trsv<T, FWD, 64, false>, hi - lo, args, s, F->chain_per_cu);
         else
             e = trsv_launch<T, FWD>(F, hi - lo, args, s);
         if (e != hipSuccess) return e;
