@@ -126,7 +126,7 @@ constexpr int64_t HEAD_DEFAULT = 4096;
 // fill up (3D grid 32^3, geometric graph of 30,000 nodes).
 constexpr int64_t CHAIN_PLAN_ROWS = 131072;
 // bound on head rows x head entries (the inverse's work grows with it): about six
-// times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.6 ms)
+// times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.3 ms)
 constexpr int64_t HEAD_COST = (int64_t)8 << 30;
 
 // Device memory from the library's kept blocks (pool.cpp).  dev_release: no work on the
