@@ -509,13 +509,21 @@ int chain_build(srw_factor* F, int64_t h, int64_t m, Arena& keep, int64_t* pinne
 {
     if (F->n + m > INT32_MAX || m * POOL_PER_ROW > INT32_MAX) return SRW_OK;  // 32-bit places
     for (int shrink = 0; shrink <= 2; ++shrink) {
-        Arena tmp;
+        Arena tmp, own;
         bool too_big = false;
-        const int st = F->precision == SRW_FP32 ? build<float>(F, h, m, shrink, keep, tmp, pinned, s, &too_big)
-                                                : build<double>(F, h, m, shrink, keep, tmp, pinned, s, &too_big);
+        const int st = F->precision == SRW_FP32 ? build<float>(F, h, m, shrink, own, tmp, pinned, s, &too_big)
+                                                : build<double>(F, h, m, shrink, own, tmp, pinned, s, &too_big);
         (void)hipStreamSynchronize(s);
         tmp.release();
-        if (st != SRW_OK || !too_big) return st;
+        if (st != SRW_OK) {
+            own.release();
+            F->chain = ChainPlan{};
+            if (st != SRW_E_NOMEM) return st;
+            (void)hipGetLastError();  // no memory for a plan: the solves do without
+            return SRW_OK;
+        }
+        keep.blocks.insert(keep.blocks.end(), own.blocks.begin(), own.blocks.end());
+        if (!too_big) return SRW_OK;
     }
     return SRW_OK;
 }
