@@ -932,7 +932,9 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
                 next = id + (uint32_t)dict[dbase + ((x1.w >> sh) & 7u)];
                 ground = sh >= 4u * deg && (x0.x & NEAR_GROUNDED) != 0;
             } else {
-                const uint32_t line = word_line<FMT>(word, u);
+                // a walk's first word is its start record's line itself, which may lie past
+                // LINE_MASK (start records follow n_lines walk lines)
+                const uint32_t line = j == 0 && t == 0 ? word : word_line<FMT>(word, u);
                 const uint4* lp = recs + (size_t)line * 4;
                 const uint4 r0 = lp[0], r1 = lp[1], r2 = lp[2], r3 = lp[3];
                 if (pend) {

@@ -1,0 +1,61 @@
+"""The walk kernel at the limits of its record formats and of its queues: every walk is the
+oracle's, bit for bit, on either side of a limit."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_math_0609672_amd import workloads as W
+from test_gpu_parity import DEV, np_, srw, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def factor_bit_exact(srw, A, walks, seed, **kw):  # noqa: F811
+    F = srw.build_factor(srw.Matrix.from_host(A, DEV), walks, 0.0, seed, **kw)
+    got = {k: np_(v) for k, v in F.export().items()}
+    ref = O.build_factor(A, walks, 0.0, seed)
+    for k in ("rank", "yptr", "ycol", "yval", "d"):
+        assert np.array_equal(got[k], getattr(ref, k)), k
+    return F
+
+
+def wide_circulant(n):
+    """Node v joined to v +- 1 .. 12: twelve neighbours of little weight between twelve of
+    much, half of every diagonal excess (walks end soon).  Four or five of the light ones
+    meet one of the 64 equal draw ranges, eight one of 32: a record has 64 bucket lines, its
+    first line and three more."""
+    off = np.concatenate([np.arange(-12, 0), [0], np.arange(1, 13)])
+    w = np.where(off == 0, 1.0, np.where(abs(off) <= 6, -0.004, -0.0375))
+    col = (np.arange(n, dtype=np.int32)[:, None] + off.astype(np.int32)) % n
+    val = np.broadcast_to(w, col.shape).copy()
+    for v in list(range(12)) + list(range(n - 12, n)):  # rows that wrap round
+        o = np.argsort(col[v])
+        col[v], val[v] = col[v][o], val[v][o]
+    return W.CSR(n, np.arange(n + 1, dtype=np.int64) * 25, col.reshape(-1), val.reshape(-1))
+
+
+def record_lines(A, v):
+    """Lines of node v's record: with k in 3..6 the first for which each of 2^k equal draw
+    ranges meets at most six entries, 2^k bucket lines; the first line; eight entries a line."""
+    p = slice(A.rowptr[v], A.rowptr[v + 1])
+    off = A.col[p] != v
+    c = np.cumsum(-A.val[p][off]) / A.val[p][~off][0]
+    deg = int(off.sum())
+    if deg <= 6:
+        return 1
+    lo = np.concatenate([[0.0], c[:-1]])
+    for k in range(3, 7) if deg <= 64 else ():
+        first = np.arange(2 ** k)[:, None] / 2 ** k
+        if ((lo < first + 0.5 ** k) & (c > first)).sum(1).max() <= 6:
+            return 2 ** k + 1 + (deg + 7) // 8
+    return 1 + (deg + 7) // 8
+
+
+# 68 lines a node: start records' lines, which follow the walk records', end below the 2^27
+# lines that an entry's line word can name (900,000) or pass them (1,040,000)
+@pytest.mark.parametrize("n", [900_000, 1_040_000])
+def test_start_records_past_the_line_mask(srw, n):  # noqa: F811
+    A = wide_circulant(n)
+    assert record_lines(A, n // 2) == 68
+    assert (2 * 68 * n > 2 ** 27) == (n > 1_000_000) and 68 * n < 2 ** 27
+    factor_bit_exact(srw, A, 2, 3)
