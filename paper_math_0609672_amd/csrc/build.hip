@@ -18,6 +18,7 @@
 #include <cstring>
 
 #include "factor.hpp"
+#include "handover.hpp"
 
 namespace srw {
 
@@ -1729,25 +1730,27 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
                 // beside the bulk waves, as far as the chip holds them (k_walk at the
                 // default refill period): more bulk waves for the slabs, then waves for
                 // handed-over walks
-                wa.n_bulk = wa.n_first = (uint32_t)(blocks * (BLOCK / 64));
+                wa.hq.n_bulk = wa.n_first = (uint32_t)(blocks * (BLOCK / 64));
                 if (hand) {
                     const int64_t room = std::max<int64_t>(0, (int64_t)cus * std::max(1, per_cu) - blocks);
                     const int64_t late = std::min(room / 2, (int64_t)cus * late_w / (BLOCK / 64));
                     const int64_t extra = std::min<int64_t>(
                         {room, late + (int64_t)cus * single_w / (BLOCK / 64), (total_walks + BLOCK - 1) / BLOCK});
                     const int64_t cap = std::min<int64_t>(total_walks, HAND_SLOTS);
-                    wa.slots = ALLOC(tmp, unsigned long long, cap * SLOT_WORDS);
-                    wa.hand = ALLOC(tmp, unsigned long long, HAND_WORDS);
-                    if (!wa.slots || !wa.hand) FAIL(SRW_E_NOMEM);
-                    wa.slot_cap = (uint32_t)cap;
-                    wa.n_bulk += (uint32_t)(std::min(late, extra) * (BLOCK / 64));
+                    wa.hq.slots = ALLOC(tmp, unsigned long long, cap * SLOT_WORDS);
+                    wa.hq.hand = ALLOC(tmp, unsigned long long, HAND_WORDS);
+                    if (!wa.hq.slots || !wa.hq.hand) FAIL(SRW_E_NOMEM);
+                    wa.hq.cap = (uint32_t)cap;
+                    wa.hq.wait_limit = wait_ticks(20.0);
+                    wa.hq.n_bulk += (uint32_t)(std::min(late, extra) * (BLOCK / 64));
                     k_fill_u64<<<std::min(grid_for(cap * SLOT_WORDS, BLOCK), 2048), BLOCK, 0, s>>>(
-                        cap * SLOT_WORDS, wa.slots, SLOT_EMPTY);
-                    k_fill_u64<<<1, BLOCK, 0, s>>>(HAND_WORDS, wa.hand, 0ull);
+                        cap * SLOT_WORDS, wa.hq.slots, SLOT_EMPTY);
+                    k_fill_u64<<<1, BLOCK, 0, s>>>(HAND_WORDS, wa.hq.hand, 0ull);
                     blocks += extra;
                     // claims small enough that every bulk wave gets work
                     wa.slab_claim = (uint32_t)std::max<int64_t>(
-                        1, std::min<int64_t>(wa.slab_claim, n_chunks / (4 * (int64_t)wa.n_bulk)));
+                        1, std::min<int64_t>(wa.slab_claim, n_chunks / (4 * (int64_t)wa.hq.n_bulk)));
+                    wa.hq.n_groups = wa.hq.n_bulk / (BLOCK / 64);
                 }
                 // the first waves' first chunks of the long segment are theirs without a claim
                 if (opt.refill_period == 8) k_fill_u64<<<1, 1, 0, s>>>(1, queue, wa.n_first);

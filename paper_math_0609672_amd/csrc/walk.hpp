@@ -451,13 +451,9 @@ struct WalkArgs {
     uint32_t* rec_len;
     unsigned long long* queue;  // chunks taken of every segment, QUEUE_STRIDE words apart
     uint32_t slab_claim;       // chunks a wave claims at once from a slab queue (>= 1)
-    // long walks handed over to single-walk waves (walk_handed_over)
-    uint32_t n_bulk;               // waves that take walks from the chunk queues
-    uint32_t n_first;              // those of them that start at once; the others once the
-                                   // long segment's rows are taken
-    uint32_t slot_cap;             // slots; 0: no walk is handed over
-    unsigned long long* slots;     // SLOT_WORDS words each, SLOT_EMPTY before the launch
-    unsigned long long* hand;      // HAND_WORDS control words, zero before the launch
+    uint32_t n_first;          // bulk waves that start at once; the others once the long
+                               // segment's rows are taken
+    HandQueue hq;              // long walks handed over to single-walk waves
     unsigned long long* deg_sum;
     int* err;
     // walk reuse: per-lane stacks of stack_depth entries {rank, node, position,
@@ -543,20 +539,6 @@ __device__ __forceinline__ void emit_walks(const WalkArgs& a, bool em, uint32_t 
 // 0.42 us on the graph (idle chip).  Walk kernel with walks handed over, on the same
 // records: graph 780 -> 480 ms; grid 64^3 70 -> 34 ms; the grid 128^3 is bound by the
 // bulk waves.
-//
-// Slots are handed out in order (tail) and taken in order (head, the tickets); a slot's
-// words are each their own ready flag.  A ticket past the tail is a wave waiting for
-// work: it polls its own slot only (thousands of waves polling one address hold up every
-// atomic on that channel by tens of microseconds).  The last bulk wave to finish marks
-// the slots of the tickets past the tail as closed.
-constexpr int SLOT_WORDS = 4;  // {chunk | walk << 32, step << 32 | line word, visits, -}
-constexpr unsigned long long SLOT_EMPTY = ~0ull, SLOT_CLOSED = ~1ull;
-enum : int {
-    HAND_QUEUE = 0,     // tail | head << 32
-    HAND_ARRIVED = 32,  // bulk workgroups that have started
-    HAND_DONE = 64,     // bulk waves that have finished
-    HAND_WORDS = 96
-};
 constexpr uint32_t HAND_MIN_AGE = 64;   // steps before a walk may move
 constexpr uint32_t HAND_GROUPS = 8;     // groups of eight steps between a bulk wave's looks
 constexpr int HAND_WAITING = 256;       // walks kept waiting for a free wave
@@ -567,6 +549,39 @@ __device__ __forceinline__ unsigned long long hand_load(const unsigned long long
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// The hand-over queue's memory operations on the device.
+struct HandMem {
+    __device__ __forceinline__ uint64_t load(const unsigned long long* p) const
+    {
+        return readfirstlane64(hand_load(p));
+    }
+    __device__ __forceinline__ void store(unsigned long long* p, unsigned long long v) const
+    {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint64_t add(unsigned long long* p, unsigned long long v) const
+    {
+        return wave_fetch_add(p, v);
+    }
+    __device__ __forceinline__ uint64_t cas(unsigned long long* p, unsigned long long from,
+                                            unsigned long long to) const
+    {
+        return atomicCAS(p, from, to);
+    }
+    // lane 0's, the same in every lane
+    __device__ __forceinline__ uint64_t cas_uniform(unsigned long long* p, unsigned long long from,
+                                                    unsigned long long to) const
+    {
+        unsigned long long r = 0;
+        if (__lane_id() == 0) r = atomicCAS(p, from, to);
+        return lane0_u64(r);
+    }
+    __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(32); }
+    __device__ __forceinline__ int64_t now() const { return wall_clock64(); }
+    __device__ __forceinline__ uint32_t lane() const { return __lane_id(); }
+    __device__ __forceinline__ uint32_t lanes() const { return 64u; }
+};
 
 // Wave-uniform data of an earlier launch, through the scalar cache.
 template <typename V>
@@ -721,26 +736,11 @@ __device__ __forceinline__ void walk_handed_over(const WalkArgs& a)
 {
     uint64_t degsum = 0;
     __builtin_amdgcn_s_setprio(3);  // few instructions per step, all of them on the chain
-    for (;;) {
-        const uint32_t ticket = (uint32_t)(wave_fetch_add(a.hand + HAND_QUEUE, 1ull << 32) >> 32);
-        if (ticket >= a.slot_cap) break;
-        const unsigned long long* slot = a.slots + (size_t)ticket * SLOT_WORDS;
-        uint64_t w0 = readfirstlane64(hand_load(slot)), w1, w2;
-        if (w0 == SLOT_EMPTY && readfirstlane64(hand_load(a.hand + HAND_DONE)) >= a.n_bulk &&
-            ticket >= (uint32_t)readfirstlane64(hand_load(a.hand + HAND_QUEUE)))
-            break;  // the tail is final and this ticket, taken after it was, is past it
-        while (w0 == SLOT_EMPTY) {
-            __builtin_amdgcn_s_sleep(32);
-            w0 = readfirstlane64(hand_load(slot));
-        }
-        if (w0 == SLOT_CLOSED) break;
-        do {  // the other words are there or on their way
-            w1 = readfirstlane64(hand_load(slot + 1));
-            w2 = readfirstlane64(hand_load(slot + 2));
-        } while (w1 == SLOT_EMPTY || w2 == SLOT_EMPTY);
-        const ChunkDesc cd = scalar_chunk(a.chunks, (uint32_t)w0);
-        degsum += run_single<FMT>(a, cd, (uint32_t)(w0 >> 32), (uint32_t)(w1 >> 32), (uint32_t)w1,
-                                  (uint32_t)w2);
+    HandedWalk w;
+    while (hand_take(HandMem{}, a.hq, w)) {
+        const ChunkDesc cd = scalar_chunk(a.chunks, (uint32_t)w.w0);
+        degsum += run_single<FMT>(a, cd, (uint32_t)(w.w0 >> 32), (uint32_t)(w.w1 >> 32), (uint32_t)w.w1,
+                                  (uint32_t)w.w2);
     }
     if (__lane_id() == 0 && degsum) atomicAdd(a.deg_sum, (unsigned long long)degsum);
 }
@@ -830,32 +830,27 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
         // waiting for a wave (the longest walks start first, so they are the oldest at any
         // time).  Afterwards: any walk, if a wave is idle; and the last few walks of a
         // wave all at once.
-        if (a.slot_cap != 0 && g != 0 && g % (done ? 2u : HAND_GROUPS) == 0) {
+        if (a.hq.cap != 0 && g != 0 && g % (done ? 2u : HAND_GROUPS) == 0) {
             const uint64_t act = ballot(active);
             const uint64_t cand = done ? act
                                        : ballot(active && t >= HAND_MIN_AGE && t >= 4 * g && t < 0x40000000u);
             if (cand != 0) {
                 int room = HAND_LAST;
                 if (!done || __popcll(act) > HAND_LAST) {
-                    const uint64_t qs = readfirstlane64(hand_load(a.hand + HAND_QUEUE));
+                    const uint64_t qs = readfirstlane64(hand_load(a.hq.hand + HAND_QUEUE));
                     const int waiting = (int)((uint32_t)qs - (uint32_t)(qs >> 32));
                     if (!done) room = waiting < HAND_WAITING ? HAND_PER_LOOK : 0;
                     else if (waiting >= 0) room = 0;
-                    if ((uint32_t)qs >= a.slot_cap) room = 0;
+                    if ((uint32_t)qs >= a.hq.cap) room = 0;
                 }
                 const int place = (int)__popcll(cand & lt);
                 const bool go = ((cand >> lane) & 1ull) && place < room;
                 const uint32_t cnt = (uint32_t)__popcll(ballot(go));
                 if (cnt != 0) {
-                    const uint32_t at = (uint32_t)wave_fetch_add(a.hand + HAND_QUEUE, cnt) + (uint32_t)place;
-                    if (go && at < a.slot_cap) {
-                        unsigned long long* sl = a.slots + (size_t)at * SLOT_WORDS;
-                        const unsigned long long words[3] = {
-                            (unsigned long long)cidx | (unsigned long long)w << 32,
-                            (unsigned long long)t << 32 | word, (unsigned long long)visits};
-                        for (int i = 0; i < 3; ++i)
-                            __hip_atomic_store(sl + i, words[i], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
+                    const uint32_t at = (uint32_t)wave_fetch_add(a.hq.hand + HAND_QUEUE, cnt) + (uint32_t)place;
+                    if (go && hand_put(HandMem{}, a.hq, at,
+                                       {(uint64_t)cidx | (uint64_t)w << 32, (uint64_t)t << 32 | word,
+                                        (uint64_t)visits})) {
                         active = false;
                         word = 0;
                     }
@@ -1295,27 +1290,25 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     walk_body<8, true, BUCKETS>(a);
 }
 
-// Each wave's part: a bulk wave, then (a.slot_cap) a single-walk wave.  Bulk waves wait
-// for no one while they have work.  A later workgroup waits (for the long segment to be
-// taken, for handed-over walks) only if every bulk workgroup has started, so no wait can
-// keep the chip from a wave that it depends on, in whatever order the workgroups are
-// dispatched; else a late bulk wave starts at once and a single-walk wave ends (the bulk
-// waves take over the walks handed over when they finish).
+// Each wave's part: a bulk wave, then (a.hq.cap) a single-walk wave.  A later workgroup
+// looks for a while whether every bulk workgroup has started: if not, a late bulk wave
+// starts at once, and a single-walk wave ends.
 template <int FMT>
 __device__ __forceinline__ void walk_wave(const WalkArgs& a, const uint4* recs, const int32_t* dict)
 {
     __shared__ int all_here;
-    const bool hand = a.slot_cap != 0;
+    const bool hand = a.hq.cap != 0;
+    const HandMem mem;
     const uint32_t wave = blockIdx.x * (BLOCK / 64) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool bulk = wave < a.n_bulk;
-    bool here = true;
+    const bool bulk = wave < a.hq.n_bulk;
+    bool here = false;  // known that every bulk workgroup has started
     if (hand) {
-        if (bulk && threadIdx.x == 0) atomicAdd(a.hand + HAND_ARRIVED, 1ull);
+        if (bulk && threadIdx.x == 0) atomicAdd(a.hq.hand + HAND_ARRIVED, 1ull);
         if (wave >= a.n_first) {
             if (threadIdx.x == 0) {
                 int ok = 0;
                 for (int i = 0; i < 64 && !ok; ++i) {
-                    ok = hand_load(a.hand + HAND_ARRIVED) >= a.n_bulk / (BLOCK / 64);
+                    ok = hand_load(a.hq.hand + HAND_ARRIVED) >= a.hq.n_groups;
                     if (!ok) __builtin_amdgcn_s_sleep(64);
                 }
                 all_here = ok;
@@ -1325,21 +1318,16 @@ __device__ __forceinline__ void walk_wave(const WalkArgs& a, const uint4* recs, 
         }
     }
     if (bulk) {
-        if (hand && wave >= a.n_first && here) {
+        if (here) {  // (a late wave)
             const unsigned long long size = (unsigned long long)(a.bounds[1] - a.bounds[0]);
-            while (readfirstlane64(hand_load(a.queue)) < size) __builtin_amdgcn_s_sleep(127);
+            const int64_t t0 = mem.now();
+            while (mem.load(a.queue) < size && mem.now() - t0 <= a.hq.wait_limit)
+                __builtin_amdgcn_s_sleep(127);
         }
         walk_bulk<FMT>(a, recs, dict, wave < a.n_first ? wave : ~0u);
-        if (hand && wave_fetch_add(a.hand + HAND_DONE, 1ull) == a.n_bulk - 1u) {
-            // the last one: the tickets past the tail, and their slots
-            const uint64_t qs = wave_fetch_add(a.hand + HAND_QUEUE, 0ull);
-            const uint32_t head = min((uint32_t)(qs >> 32), a.slot_cap);
-            for (uint32_t i = (uint32_t)qs + __lane_id(); i < head; i += 64)
-                __hip_atomic_store(a.slots + (size_t)i * SLOT_WORDS, SLOT_CLOSED, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        }
+        here = hand && hand_finish(mem, a.hq);
     }
-    if (hand && here) walk_handed_over<FMT>(a);
+    if (here) walk_handed_over<FMT>(a);
 }
 
 template <int FMT>

@@ -1,11 +1,13 @@
 """The walk kernel at the limits of its record formats and of its queues: every walk is the
 oracle's, bit for bit, on either side of a limit."""
+import threading
+
 import numpy as np
 import pytest
 
 import oracle as O
 from paper_math_0609672_amd import workloads as W
-from test_gpu_parity import DEV, np_, srw, torch  # noqa: F401
+from test_gpu_parity import DEV, compare_walks, np_, srw, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +61,45 @@ def test_start_records_past_the_line_mask(srw, n):  # noqa: F811
     assert record_lines(A, n // 2) == 68
     assert (2 * 68 * n > 2 ** 27) == (n > 1_000_000) and 68 * n < 2 ** 27
     factor_bit_exact(srw, A, 2, 3)
+
+
+@pytest.mark.parametrize("walk_waves", [0, 24, 64])
+def test_as_many_bulk_waves_as_the_chip_holds(srw, walk_waves):  # noqa: F811
+    """20,000 chunks: from 24 waves to a CU on the first workgroups alone fill the chip."""
+    compare_walks(srw, W.grid((160, 125), ground_frac=0.01, seed=6), 24, 4, walk_waves=walk_waves)
+
+
+def test_builds_at_once(srw):  # noqa: F811
+    """Builds of several threads and streams share the chip; three of them hold a table of more
+    than half a CU's LDS in every workgroup."""
+    mats = [W.random_graph(900, 1100, seed=4), W.random_graph(90, 420, seed=2), W.grid((160, 125), seed=3),
+            W.random_graph(1000, 1200, seed=4)]
+    for i in (0, 1, 3):
+        lines = sum(record_lines(mats[i], v) for v in range(mats[i].n))
+        assert 640 < lines < 1280
+    refs = [O.build_factor(A, 200, 0.0, i) for i, A in enumerate(mats)]
+    bad = []
+
+    def work(i):
+        try:
+            s = torch.cuda.Stream(device=DEV)
+            with torch.cuda.stream(s):
+                M = srw.Matrix.from_host(mats[i], DEV)
+                for _ in range(8):
+                    F = srw.build_factor(M, 200, 0.0, i, stream=s)
+                    got = {k: np_(v) for k, v in F.export().items()}
+                    if F.stats()["walk_lds"] != (i != 2):
+                        bad.append((i, "walk_lds"))
+                    for k in ("ycol", "yval", "d"):
+                        if not np.array_equal(got[k], getattr(refs[i], k)):
+                            bad.append((i, k))
+                    F.free()
+        except Exception as e:  # noqa: BLE001
+            bad.append((i, e))
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(len(mats))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
