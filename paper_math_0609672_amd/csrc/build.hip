@@ -1676,18 +1676,23 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             CHECK_HIP(hipGetDevice(&dev));
             CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             void (*kern)(WalkArgs) = nullptr;
-            // a table that fits in one workgroup's LDS is staged there (the default
-            // refill period only)
+            // a table that fits in one workgroup's LDS, beside what the kernel itself keeps
+            // there, is staged there (the default refill period only)
             int lds_max = 0;
             CHECK_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
             const size_t table_bytes = (size_t)(2 * n_lines) * 64;
-            const bool lds_table = !reuse && opt.refill_period == 8 && table_bytes <= (size_t)lds_max;
+            bool lds_table = !reuse && opt.refill_period == 8 && table_bytes <= (size_t)lds_max;
             size_t dyn_lds = 0;
             const int fmt = near ? REC_NEAR : bucketing ? REC_BUCKETS : REC_LINES;
             if (lds_table) {
                 kern = fmt == REC_NEAR ? k_walk_lds<REC_NEAR>
                                        : fmt == REC_BUCKETS ? k_walk_lds<REC_BUCKETS> : k_walk_lds<REC_LINES>;
                 dyn_lds = (size_t)rec_words * sizeof(uint4);
+                hipFuncAttributes fa{};
+                CHECK_HIP(hipFuncGetAttributes(&fa, (const void*)kern));
+                lds_table = fa.sharedSizeBytes + dyn_lds <= (size_t)lds_max;
+            }
+            if (lds_table) {
                 F->walk_lds = 1;
                 CHECK_HIP(hipFuncSetAttribute((const void*)kern,
                                               hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1695,6 +1700,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             } else if (reuse) {
                 kern = bucketing ? k_walk_reuse<true> : k_walk_reuse<false>;
             } else {
+                dyn_lds = 0;
                 switch (opt.refill_period) {
                     case 1: kern = bucketing ? k_walk_refill<1, true> : k_walk_refill<1, false>; break;
                     case 2: kern = bucketing ? k_walk_refill<2, true> : k_walk_refill<2, false>; break;

@@ -63,6 +63,37 @@ def test_start_records_past_the_line_mask(srw, n):  # noqa: F811
     factor_bit_exact(srw, A, 2, 3)
 
 
+def chorded_path(n, hub):
+    """A path whose nodes are joined in random pairs (narrow records on many diagonals); with
+    hub, node 5 is joined to six more (a record with bucket lines)."""
+    rng = np.random.default_rng(n)
+    p = rng.permutation(np.arange(20, n))
+    p = np.sort(p[: p.size // 2 * 2].reshape(-1, 2), axis=1)
+    p = p[p[:, 1] > p[:, 0] + 1]
+    far = n - 10 * np.arange(1, 7) if hub else np.zeros(0, np.int64)
+    eu = np.concatenate([np.arange(n - 1), p[:, 0], np.full(far.size, 5)])
+    ev = np.concatenate([np.arange(1, n), p[:, 1], far])
+    exc = np.where(np.arange(n) % 40 == 0, 0.5, 0.0)
+    return W.assemble(n, eu, ev, np.ones(eu.size), exc)
+
+
+# 1,280 lines are 160 KiB with their start records: all of a workgroup's LDS, of which the
+# kernel needs a little for itself
+@pytest.mark.parametrize("lines", [1279, 1280, 1281])
+@pytest.mark.parametrize("kind", ["near", "lines", "buckets"])
+def test_tables_at_the_size_of_the_lds(srw, kind, lines):  # noqa: F811
+    if kind == "near":
+        A = W.grid((lines,), ground_frac=0.05, seed=2)
+    else:
+        hub = kind == "buckets"
+        A = chorded_path(lines - 9 if hub else lines, hub)
+        assert record_lines(A, 5) == (10 if hub else 1)
+        assert np.unique(A.col - np.repeat(np.arange(A.n), np.diff(A.rowptr))).size > 9
+    assert sum(record_lines(A, v) for v in range(A.n)) == lines
+    F = factor_bit_exact(srw, A, 40, 7)
+    assert F.stats()["walk_lds"] == (lines <= (1280 if kind == "near" else 1279))
+
+
 @pytest.mark.parametrize("walk_waves", [0, 24, 64])
 def test_as_many_bulk_waves_as_the_chip_holds(srw, walk_waves):  # noqa: F811
     """20,000 chunks: from 24 waves to a CU on the first workgroups alone fill the chip."""
