@@ -52,6 +52,17 @@ __device__ __forceinline__ bool hand_all_started(const M& m, const HandQueue& q)
     return m.load(q.hand + HAND_ARRIVED) >= q.n_groups;
 }
 
+// The first of n slots for the wave's walks; full once the slots are used up.  A wave that
+// has seen that asks for no more, so the tail never passes cap by more than each wave's last
+// n: carried into the head, it would hand out slots again.
+template <class M>
+__device__ __forceinline__ uint32_t hand_reserve(const M& m, const HandQueue& q, uint32_t n, bool& full)
+{
+    const uint32_t at = (uint32_t)m.add(q.hand + HAND_QUEUE, n);
+    full = at >= q.cap;
+    return at;
+}
+
 // A lane's walk into slot `at`; false (the lane keeps it) past the last slot, or if the
 // slot's ticket holder has left.
 template <class M>

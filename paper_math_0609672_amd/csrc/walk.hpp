@@ -811,7 +811,7 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
     cur.first = first;
     ChunkDesc cd{};
     uint32_t c_next = 0, c_end = 0;
-    bool done = false;
+    bool done = false, full = a.hq.cap == 0;  // full: no slot is left, or will be
     // per-lane walk state
     bool active = false, pend = false;
     uint32_t key = 0, w = 0, t = 0, visits = 0, rank_k = 0, cidx = 0, word = 0, dbase = 0;
@@ -830,7 +830,7 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
         // waiting for a wave (the longest walks start first, so they are the oldest at any
         // time).  Afterwards: any walk, if a wave is idle; and the last few walks of a
         // wave all at once.
-        if (a.hq.cap != 0 && g != 0 && g % (done ? 2u : HAND_GROUPS) == 0) {
+        if (!full && g != 0 && g % (done ? 2u : HAND_GROUPS) == 0) {
             const uint64_t act = ballot(active);
             const uint64_t cand = done ? act
                                        : ballot(active && t >= HAND_MIN_AGE && t >= 4 * g && t < 0x40000000u);
@@ -841,13 +841,14 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
                     const int waiting = (int)((uint32_t)qs - (uint32_t)(qs >> 32));
                     if (!done) room = waiting < HAND_WAITING ? HAND_PER_LOOK : 0;
                     else if (waiting >= 0) room = 0;
-                    if ((uint32_t)qs >= a.hq.cap) room = 0;
+                    full = (uint32_t)qs >= a.hq.cap;
+                    if (full) room = 0;
                 }
                 const int place = (int)__popcll(cand & lt);
                 const bool go = ((cand >> lane) & 1ull) && place < room;
                 const uint32_t cnt = (uint32_t)__popcll(ballot(go));
                 if (cnt != 0) {
-                    const uint32_t at = (uint32_t)wave_fetch_add(a.hq.hand + HAND_QUEUE, cnt) + (uint32_t)place;
+                    const uint32_t at = hand_reserve(HandMem{}, a.hq, cnt, full) + (uint32_t)place;
                     if (go && hand_put(HandMem{}, a.hq, at,
                                        {(uint64_t)cidx | (uint64_t)w << 32, (uint64_t)t << 32 | word,
                                         (uint64_t)visits})) {

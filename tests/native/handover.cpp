@@ -3,7 +3,8 @@
 // Arguments: bulk waves, single-walk waves, waves held at once, walks, slots, wait limit (ns,
 // 0: none), start order (0: as launched, 1: shuffled), seed, 1 to let bulk waves wait without
 // asking whether all have started.  Prints the walks lost, the walks run twice and "stalled"
-// if every running wave has waited in vain for two seconds.
+// if every running wave has waited in vain for two seconds; on stderr, how far the tail is past
+// the last slot.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -87,6 +88,7 @@ void done(Run& r, int w)
 void bulk(Run& r, const Mem& m)
 {
     std::vector<int> mine;
+    bool full = r.q.cap == 0;
     for (bool more = true;;) {
         while (more && mine.size() < 4) {
             const int w = r.next.fetch_add(1);
@@ -95,8 +97,8 @@ void bulk(Run& r, const Mem& m)
         }
         if (mine.empty()) break;
         const size_t k = (*m.rng)() % mine.size();
-        if ((*m.rng)() % 2 == 0) {
-            const uint32_t at = (uint32_t)m.add(r.q.hand + HAND_QUEUE, 1);
+        if (!full && (*m.rng)() % 2 == 0) {
+            const uint32_t at = hand_reserve(m, r.q, 1, full);
             if (!hand_put(m, r.q, at, {(uint64_t)mine[k], (uint64_t)mine[k] + 7, (uint64_t)mine[k] + 9})) continue;
         } else {
             done(r, mine[k]);
@@ -164,6 +166,8 @@ int main(int argc, char** argv)
     for (auto& t : held) t.join();
     int lost = 0, twice = 0;
     for (auto& n : r.ran) lost += n.load() == 0, twice += n.load() > 1;
+    const uint32_t tail = (uint32_t)hand[HAND_QUEUE];
     std::printf("%d %d%s\n", lost, twice, stalled.load() ? " stalled" : "");
+    std::fprintf(stderr, "%u\n", tail > r.q.cap ? tail - r.q.cap : 0u);
     return 0;
 }

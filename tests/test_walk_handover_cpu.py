@@ -16,10 +16,11 @@ def model(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_math_0609672_amd", "csrc"),
                     os.path.join(ROOT, "tests", "native", "handover.cpp"), "-o", exe], check=True)
 
-    def run(bulk, single, held, walks, slots, limit=0, order=0, seed=0, unasked=0):
+    def run(bulk, single, held, walks, slots, limit=0, order=0, seed=0, unasked=0, tail=False):
         args = [bulk, single, held, walks, slots, limit, order, seed, unasked]
-        return subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True,
-                              check=True, timeout=60).stdout.split()
+        r = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True,
+                           check=True, timeout=60)
+        return int(r.stderr) if tail else r.stdout.split()
 
     return run
 
@@ -42,3 +43,9 @@ def test_waves_that_leave_lose_no_walk(model, limit, bulk, single, held):
 def test_a_wait_for_waves_not_started_would_stall(model):
     """What the rule is for: bulk waves that wait without asking hold the chip."""
     assert model(12, 8, 4, 400, 400, unasked=1)[-1] == "stalled"
+
+
+@pytest.mark.parametrize("slots", [0, 1, 40])
+def test_the_tail_stays_near_the_last_slot(model, slots):
+    """However many walks find no slot: each wave asks once more at most."""
+    assert model(6, 4, 10, 20_000, slots, tail=True) <= 6
