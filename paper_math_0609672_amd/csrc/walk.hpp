@@ -473,6 +473,13 @@ struct WalkArgs {
 
 constexpr uint32_t REUSE_CHUNK = 4096;
 
+// The step cap of a walk whose steps are counted in 32 bits (by eights: the count stops short
+// of wrapping round, or a walk that never ends would run for good).
+__device__ __forceinline__ uint32_t step_limit(const WalkArgs& a)
+{
+    return (uint32_t)(a.max_steps < 0xFFFFFF00ull ? a.max_steps : 0xFFFFFF00ull);
+}
+
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
 {
     const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)v, src);
@@ -643,7 +650,7 @@ __device__ __forceinline__ uint64_t run_single(const WalkArgs& a, const ChunkDes
                                                uint32_t t, uint32_t word, uint32_t visits)
 {
     const int lane = __lane_id();
-    const uint64_t limit = a.max_steps;
+    const uint32_t limit = step_limit(a);
     int32_t dl = 0;  // near records: lane i holds the matrix's diagonal i
     if (FMT == REC_NEAR && lane < NEAR_DELTAS)
         dl = a.delta[(cd.walks >> WALKS_MAT_SHIFT) * NEAR_DELTAS + lane];
@@ -805,7 +812,7 @@ __device__ __forceinline__ void walk_bulk(const WalkArgs& a, const uint4* recs, 
     const int lane = __lane_id();
     const uint64_t lt = lanemask_lt();
     const int home_slab = (int)(blockIdx.x % NSLAB);
-    const uint32_t limit = (uint32_t)(a.max_steps < 0xFFFFFF00ull ? a.max_steps : 0xFFFFFF00ull);
+    const uint32_t limit = step_limit(a);
     // wave-uniform chunk state
     ChunkCursor cur;
     cur.first = first;

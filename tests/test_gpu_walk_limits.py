@@ -134,3 +134,9 @@ def test_builds_at_once(srw):  # noqa: F811
     for t in ts:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("max_steps", [2 ** 32 - 256, 2 ** 32, 2 ** 64 - 1])
+def test_step_caps_past_32_bits(srw, max_steps):  # noqa: F811
+    """Walks of both kinds of wave under the largest caps."""
+    factor_bit_exact(srw, W.grid((40, 37), ground_frac=0.001, seed=8), 24, 3, max_steps=max_steps)
