@@ -62,6 +62,26 @@ size_t size_class(size_t bytes)
     return (bytes + step - 1) / step * step;
 }
 
+// Allocates and frees although some stream of the process, another thread's or this one's,
+// may be under capture: nothing of it enters the graph.
+struct OutsideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+hipError_t raw_alloc(void** p, size_t bytes)
+{
+    const OutsideCaptures o;
+    return hipMalloc(p, bytes);
+}
+
+void raw_free(void* p)
+{
+    const OutsideCaptures o;
+    (void)hipFree(p);
+}
+
 }  // namespace
 
 hipError_t dev_alloc(void** out, size_t bytes)
@@ -93,18 +113,18 @@ hipError_t dev_alloc(void** out, size_t bytes)
             }
         }
         void* p = nullptr;
-        e = hipMalloc(&p, need);
+        e = raw_alloc(&p, need);
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             dev_trim(dev);
-            e = hipMalloc(&p, need);
+            e = raw_alloc(&p, need);
         }
         if (e != hipSuccess) return e;
         try {
             std::lock_guard<std::mutex> lk(P.mu);
             P.live.emplace(p, Owner{dev, need});
         } catch (...) {
-            (void)hipFree(p);
+            raw_free(p);
             throw;
         }
         *out = p;
@@ -150,8 +170,8 @@ void dev_release(void* p)
         D.kept.erase(D.kept.begin(), D.kept.begin() + (std::ptrdiff_t)n);
     } catch (...) {
     }
-    if (lost) (void)hipFree(p);
-    for (void* q : back) (void)hipFree(q);
+    if (lost) raw_free(p);
+    for (void* q : back) raw_free(q);
 }
 
 void dev_trim(int dev)
@@ -164,7 +184,7 @@ void dev_trim(int dev)
         back.swap(D.kept);
         D.bytes = 0;
     }
-    for (const Block& b : back) (void)hipFree(b.p);
+    for (const Block& b : back) raw_free(b.p);
 }
 
 }  // namespace srw

@@ -1,5 +1,8 @@
 """Device memory kept between calls: results do not depend on what earlier calls left in it,
 several threads share it, and it stays bounded."""
+import os
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -79,3 +82,40 @@ def test_repeated_builds_do_not_grow(srw):
     torch.cuda.synchronize()
     free1, _ = torch.cuda.mem_get_info()
     assert free0 - free1 < 256 << 20
+
+
+FEATURES_DURING_CAPTURE = """
+import os, threading, torch
+from paper_math_0609672_amd import srw, workloads as W
+A = W.grid((90, 70), seed=1)
+M = srw.Matrix.from_host(A, "cuda:0")
+rank = torch.randperm(A.n, device="cuda:0").int()
+one, out, got = torch.ones(1000, device="cuda:0"), torch.zeros(1000, device="cuda:0"), []
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g, capture_error_mode="global"):
+    out.copy_(one * 2)
+    t = threading.Thread(target=lambda: got.append(srw.row_features(M, rank)))
+    t.start()
+    t.join()
+    out.add_(1)
+for k in range(3):
+    out.zero_()
+    g.replay()
+    torch.cuda.synchronize()
+    assert bool((out == 3).all())
+    assert torch.equal(got[0], srw.row_features(M, rank))
+print("done", flush=True)
+os._exit(0)
+"""
+
+
+def test_a_call_while_another_thread_captures(srw):
+    """The first call of a process, whose workspace is new memory, in one thread while another
+    captures a graph in torch's default mode: both succeed.  (A process of its own has no kept
+    blocks.  The call makes no cooperative launch: the runtime refused one in a child of a
+    process that had made some.)"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FEATURES_DURING_CAPTURE], capture_output=True, text=True, cwd=root,
+                       timeout=100)
+    assert r.returncode == 0 and r.stdout.split()[-1:] == ["done"], r.stderr[-2000:]
