@@ -651,7 +651,7 @@ int mlp_train_impl(float* P, float* m, float* v, int32_t step, float lr, const f
     const int64_t nparts = std::min<int64_t>((int64_t)grid * (BLOCK / 64), (n + 15) / 16);
     float* part = nullptr;
     keep_stream_pool();
-    SRW_HIP(hipMallocAsync((void**)&part, nparts * PART * sizeof(float), s));
+    SRW_HIP(stream_alloc((void**)&part, nparts * PART * sizeof(float), s));
     const float inv = 1.0f / (float)n;
     k_mlp_grad<<<grid, BLOCK, 0, s>>>(P, musd, feat, target, rows, n_rows, n, inv, part);
     k_mlp_reduce<<<(NPARAM + 1 + 63) / 64, 64 * REDUCE_WAVES, 0, s>>>(
@@ -785,7 +785,7 @@ int mlp_standardize_impl(const float* feat, const float* target, int64_t n, floa
 {
     double* ws = nullptr;
     keep_stream_pool();
-    SRW_HIP(hipMallocAsync((void**)&ws, (STD_BLOCKS * NS + NF) * sizeof(double), s));
+    SRW_HIP(stream_alloc((void**)&ws, (STD_BLOCKS * NS + NF) * sizeof(double), s));
     double* mean = ws + STD_BLOCKS * NS;
     const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(STD_BLOCKS, (n + BLOCK - 1) / BLOCK));
     for (int pass = 0; pass < 2; ++pass) {

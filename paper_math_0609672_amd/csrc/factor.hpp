@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "pool.hpp"
 
 // Library-owned preconditioner.  Node labels are the caller's row indices; Y is
 // stored by rows (CSR, ascending node id per row, strictly lower in rank).  The
@@ -128,13 +129,6 @@ constexpr int64_t CHAIN_PLAN_ROWS = 131072;
 // bound on head rows x head entries (the inverse's work grows with it): about six
 // times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.3 ms)
 constexpr int64_t HEAD_COST = (int64_t)8 << 30;
-
-// Device memory from the library's kept blocks (pool.cpp).  dev_release: no work on the
-// block may be pending (the caller has synchronised); it may be called from any thread.
-// dev_trim gives every kept block back to the device.
-hipError_t dev_alloc(void** out, size_t bytes);
-void dev_release(void* p);
-void dev_trim(int dev);
 
 // Device allocations tracked by an owner list (released together).  With a chunk size, requests up to half a chunk are carved out of shared chunks
 // (256-byte aligned), larger ones get a block of their own.

@@ -15,7 +15,7 @@
 #include <unordered_map>
 #include <vector>
 
-#include "factor.hpp"
+#include "pool.hpp"
 
 namespace srw {
 
@@ -185,6 +185,18 @@ void dev_trim(int dev)
         D.bytes = 0;
     }
     for (const Block& b : back) raw_free(b.p);
+}
+
+hipError_t stream_alloc(void** out, size_t bytes, hipStream_t s)
+{
+    hipError_t e = hipMallocAsync(out, bytes, s);
+    int dev = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES) {
+        (void)hipGetLastError();
+        dev_trim(dev);
+        e = hipMallocAsync(out, bytes, s);
+    }
+    return e;
 }
 
 }  // namespace srw
