@@ -119,3 +119,26 @@ def test_a_call_while_another_thread_captures(srw):
     r = subprocess.run([sys.executable, "-c", FEATURES_DURING_CAPTURE], capture_output=True, text=True, cwd=root,
                        timeout=100)
     assert r.returncode == 0 and r.stdout.split()[-1:] == ["done"], r.stderr[-2000:]
+
+
+def test_repeated_large_builds_do_not_grow(srw):
+    """24 builds of tens of megabytes each, of slightly different sizes: one factor more than
+    after the first four at most (a block of another size class here and there)."""
+    A = W.grid((400, 400), seed=2)
+    M = srw.Matrix.from_host(A, DEV)
+
+    def build(seed):
+        F = srw.build_factor(M, 24, 0.0, seed)
+        size = 24 * F.stats()["nnz_y"] + 32 * A.n  # entries of Y by rows and by columns, row data
+        F.free()
+        return size
+
+    size = max(build(i) for i in range(4))
+    assert size > 20 << 20
+    torch.cuda.synchronize()
+    free0, _ = torch.cuda.mem_get_info()
+    for i in range(4, 28):
+        build(i)
+    torch.cuda.synchronize()
+    free1, _ = torch.cuda.mem_get_info()
+    assert free0 - free1 <= size
