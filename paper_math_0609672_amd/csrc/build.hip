@@ -989,7 +989,7 @@ int64_t chain_rows(int64_t n) { return std::max<int64_t>(65536, n / 8); }
 // 5,876, 4 to a CU 2,179 / 826 / 6,351; 32 lanes to a row 2,306 / 897 / 5,920.  Where it
 // takes all rows past the head, Laplace 50^3 / grid 48^3 / geometric graph of 30,000 nodes /
 // 2D grid 300^2: 2 to a CU 454 / 691 / 905 / 360, 4 432 / 704 / 979 / 338, 7 449 / 752 /
-// 1,093 / 338.  (Other orderings, whose chain runs through all rows, take all that fit.)
+// 1,093 / 338.
 constexpr int32_t CHAIN_PER_CU = 2;
 constexpr int32_t ALL_PER_CU = 4;
 // Fewer rows than this past them are not worth a launch of their own.
@@ -2172,6 +2172,9 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         }
         F->chain_end = n;
         F->head = head;
+        // (long rows by levels, or without a head, gain from a wave each: geometric graph of
+        // 100,000 nodes, 32 walks, level order 605 us an application, 694 by row length)
+        if (!ic0 && (opt.ordering == SRW_ORDER_RANDOM || opt.solve_order == 1)) F->chain_per_cu = 64;
         if (opt.solve_order != 1 && !batch && !ic0 && opt.head_rows >= 0 &&
             (opt.ordering == SRW_ORDER_RANDOM || (asym && opt.ordering == SRW_ORDER_GIVEN))) {
             if (n - head >= CHAIN_PLAN_ROWS) {

@@ -61,10 +61,11 @@ struct srw_factor {
     // by rows (row i: X[i][0..i] at i(i+1)/2), and its transpose packed by rows (row j:
     // X[j..head-1][j] at j head - j(j-1)/2)
     int64_t head = 0;
-    // the slots before this one hold most of the solves' dependency chain and are
+    // the slots before chain_end hold most of the solves' dependency chain and are
     // substituted by a launch of their own (n: one launch for all)
     int64_t chain_end = 0;
-    int32_t chain_per_cu = 64;  // workgroups per CU of that launch, at most
+    int32_t chain_per_cu = 0;  // workgroups per CU of that launch, at most, a wave per row
+                               // (0: as many as fit, lanes by row length)
     ChainPlan chain;
     void* hx = nullptr;
     void* hxt = nullptr;

@@ -786,8 +786,14 @@ hipError_t trsv_launch(const srw_factor* F, int64_t rows, void** args, hipStream
 
 int fill_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(grid_for(n, BLOCK), 1), 2048); }
 
-// The substitution over slots h..n-1 of one triangle of the plan, in two launches: the
-// slots before chain_end hold most of the dependency chain, the others most of the work.
+// The substitution over slots h..n-1 of one triangle of the plan.  In random order in two
+// launches: the slots before chain_end hold most of the dependency chain, the others most of
+// the work.  In given and natural orders the chain runs through all rows, in one launch with
+// lanes by row length: a wave per row, as for the chain, takes longer here, and longer than in
+// a kernel for waves per row alone (IC(0) in natural order, one application, in us, that
+// kernel / a wave per row / by row length: 2D grid 300^2 2,047 / 2,343 / 1,509, Laplace 50^3
+// 2,279 / 2,598 / 825, 64^3 1,850 / 2,010 / 1,010; the walks' factors in natural order: 2D
+// grid 300^2 20,936 / 23,340 / 16,655, asymmetric 40^3 2,705 / 2,998 / 1,933).
 template <typename T, bool FWD>
 hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T* w, T* sol, double* out,
                       int* err, hipStream_t s)
@@ -809,7 +815,7 @@ hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T
         hipError_t e;
         if (plan)
             e = coop_launch(k_trsv<T, FWD, 64, true>, hi, args, s, F->chain_per_cu);
-        else if (chain)
+        else if (chain && F->chain_per_cu > 0)
             e = coop_launch(k_trsv<T, FWD, 64, false>, hi - lo, args, s, F->chain_per_cu);
         else
             e = trsv_launch<T, FWD>(F, hi - lo, args, s);

@@ -85,3 +85,21 @@ def test_chain_plan_of_two_games(srw):  # noqa: F811
         _, rx, _, _ = O.bicgstab(A, ref, b, 0.0, k)
         assert np.linalg.norm(np_(x) - rx) <= 1e-10 * np.linalg.norm(rx)
     F.free()
+
+
+# orders that are not the library's random one: one launch over all rows, lanes by row length
+@pytest.mark.parametrize("walks,drop,lo,hi", [(16, 1e-2, 0, 28), (64, 1e-3, 28, 56), (1024, 0.0, 56, 1e9)])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
+def test_natural_order_matches_oracle(srw, walks, drop, lo, hi, precision, tol):  # noqa: F811
+    """Chains through all rows, without and behind a dense head: the bound of every apply test."""
+    A = W.grid((17, 19, 21), ground_frac=0.005, seed=3)
+    ref = O.build_factor(A, walks, drop, 7, rk=np.arange(A.n, dtype=np.int32), threads=8)
+    assert lo * A.n < ref.ycol.size <= hi * A.n
+    r = W.rhs(A.n, seed=5)
+    z = O.apply(ref, r)
+    M = srw.Matrix.from_host(A, DEV)
+    for head in (-1, 512, 0):
+        F = srw.build_factor(M, walks, drop, 7, rank="natural", precision=precision, head_rows=head)
+        got = np_(srw.apply(F, torch.as_tensor(r, device=DEV)))
+        assert np.linalg.norm(got - z) <= tol * np.linalg.norm(z), head
+        F.free()
