@@ -1343,7 +1343,8 @@ int ordering_impl(int64_t n, uint64_t seed, int32_t* rank, hipStream_t s)
 
 int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uint64_t seed,
                       const srw_options* opt_in, srw_factor** out, hipStream_t s,
-                      const BatchKeys* batch, const LengthRule* rule, bool asym, bool ic0)
+                      const BatchKeys* batch, const LengthRule* rule, bool asym, bool ic0,
+                      bool random_rank)
 {
     srw_options opt;
     srw_default_options(&opt);
@@ -2172,11 +2173,11 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         }
         F->chain_end = n;
         F->head = head;
+        const bool random = opt.ordering == SRW_ORDER_RANDOM || random_rank;
         // (long rows by levels, or without a head, gain from a wave each: geometric graph of
         // 100,000 nodes, 32 walks, level order 605 us an application, 694 by row length)
-        if (!ic0 && (opt.ordering == SRW_ORDER_RANDOM || opt.solve_order == 1)) F->chain_per_cu = 64;
-        if (opt.solve_order != 1 && !batch && !ic0 && opt.head_rows >= 0 &&
-            (opt.ordering == SRW_ORDER_RANDOM || (asym && opt.ordering == SRW_ORDER_GIVEN))) {
+        if (!ic0 && (random || opt.solve_order == 1)) F->chain_per_cu = 64;
+        if (opt.solve_order != 1 && !batch && !ic0 && opt.head_rows >= 0 && random) {
             if (n - head >= CHAIN_PLAN_ROWS) {
                 status = chain_build(F, head, CHAIN_PLAN_ROWS, keep, pinned, s);
                 if (status) goto done;

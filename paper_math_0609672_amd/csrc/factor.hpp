@@ -197,11 +197,12 @@ struct LengthRule {
 constexpr int SRW_WALKS_ONLY = 100;
 
 // asym: the matrix's values need not be symmetric (its pattern must be); used for
-// each game of an asymmetric matrix
+// each game of an asymmetric matrix.  random_rank: opt's given rank is a random order that
+// the library drew (the second game takes the first's)
 int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uint64_t seed,
                       const srw_options* opt, srw_factor** out, hipStream_t s,
                       const BatchKeys* batch = nullptr, const LengthRule* rule = nullptr,
-                      bool asym = false, bool ic0 = false);
+                      bool asym = false, bool ic0 = false, bool random_rank = false);
 // Asymmetric A (Section 7.1): the game of A, then the game of A^T with its ordering.
 int build_ldu_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uint64_t seed,
                    const srw_options* opt, srw_factor** out, hipStream_t s);

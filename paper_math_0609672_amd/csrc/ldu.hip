@@ -286,7 +286,8 @@ int build_ldu_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, uin
     ot.ordering = SRW_ORDER_GIVEN;
     ot.rank = F->rank;
     srw_factor* G = nullptr;
-    st = build_factor_impl(&At, walks_per_row, drop_tol, seed, &ot, &G, s, nullptr, nullptr, true);
+    st = build_factor_impl(&At, walks_per_row, drop_tol, seed, &ot, &G, s, nullptr, nullptr, true, false,
+                           opt.ordering == SRW_ORDER_RANDOM);
     (void)hipStreamSynchronize(s);
     dev_release(ws);
     if (st != SRW_OK) {

@@ -103,3 +103,21 @@ def test_natural_order_matches_oracle(srw, walks, drop, lo, hi, precision, tol):
         got = np_(srw.apply(F, torch.as_tensor(r, device=DEV)))
         assert np.linalg.norm(got - z) <= tol * np.linalg.norm(z), head
         F.free()
+
+
+@pytest.mark.parametrize("order", ["natural", "given"])
+def test_two_games_in_given_orders(srw, order):  # noqa: F811
+    """As many rows as the random order's plan is tried for: no plan, the oracle's iterates."""
+    A = W.grid_asym((53, 51, 52), ground_frac=0.05, seed=3)
+    rk = np.arange(A.n, dtype=np.int32)
+    if order == "given":
+        rk = np.random.default_rng(2).permutation(rk).astype(np.int32)
+    ref = O.build_factor_ldu(A, 16, 1e-2, 7, rk=rk)
+    M = srw.Matrix.from_host(A, DEV)
+    F = srw.build_factor_ldu(M, 16, 1e-2, 7, rank="natural" if order == "natural" else torch.as_tensor(rk, device=DEV))
+    b = W.rhs(A.n, seed=5)
+    for k in (1, 2):
+        _, x, _, _ = srw.bicgstab_solve(M, F, torch.as_tensor(b, device=DEV), 0.0, k)
+        _, rx, _, _ = O.bicgstab(A, ref, b, 0.0, k)
+        assert np.linalg.norm(np_(x) - rx) <= 1e-10 * np.linalg.norm(rx)
+    F.free()
