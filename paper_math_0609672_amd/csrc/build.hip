@@ -992,6 +992,16 @@ int64_t chain_rows(int64_t n) { return std::max<int64_t>(65536, n / 8); }
 // 1,093 / 338.
 constexpr int32_t CHAIN_PER_CU = 2;
 constexpr int32_t ALL_PER_CU = 4;
+// Where the rows that hold the chain are short, one launch over all rows past the head, as
+// many workgroups as fit, lanes by the mean length of the first eighth of them, takes less
+// than the plan.  One application, in us, with the plan / with 16 / 32 / 64 lanes (first
+// eighth's mean length): asymmetric 64^3, 256 walks (4.6) 403 / 311 / 324 / 354; Laplace 100^3,
+// 24 walks (15.5) 997 / 962 / 992 / 1,131; 110^3, 32 walks (15.9) 1,095 / 1,023 / 1,089 / 1,318;
+// 64^3, 48 walks (19.2) 612 / 584 / 579 / 611; 110^3, 48 walks (20.8) 1,087 / 1,287 / 1,265 /
+// 1,483; 110^3, 64 walks (24.9) 1,142 / 1,529 / 1,399 / 1,599.  Between 32 and 64 lanes the
+// line lies higher: 64^3, 256 walks (49.8) - / 1,489 / 1,199 / 1,127, geometric graph of
+// 100,000 nodes (35.2) - / 1,019 / 758 / 763.
+constexpr double LANES16_LEN = 18.0, LANES32_LEN = 44.0;
 // Fewer rows than this past them are not worth a launch of their own.
 constexpr int64_t WIDE_MIN_ROWS = 65536;
 
@@ -2173,18 +2183,32 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         }
         F->chain_end = n;
         F->head = head;
-        const bool random = opt.ordering == SRW_ORDER_RANDOM || random_rank;
-        // (long rows by levels, or without a head, gain from a wave each: geometric graph of
-        // 100,000 nodes, 32 walks, level order 605 us an application, 694 by row length)
-        if (!ic0 && (random || opt.solve_order == 1)) F->chain_per_cu = 64;
-        if (opt.solve_order != 1 && !batch && !ic0 && opt.head_rows >= 0 && random) {
-            if (n - head >= CHAIN_PLAN_ROWS) {
+        if (opt.solve_order == 1 || batch) {
+            // (long rows by levels gain from a wave each: geometric graph of 100,000 nodes,
+            // 32 walks: 605 us an application, 694 by mean row length)
+            F->chain_per_cu = 64;
+        } else if (n > head) {
+            const bool random = (opt.ordering == SRW_ORDER_RANDOM || random_rank) && !ic0 && opt.head_rows >= 0;
+            const bool large = n - head >= CHAIN_PLAN_ROWS;
+            double chain_len = 0.0;  // mean length of the first eighth of the rows past the head
+            if (!random || large) {
+                const int64_t eighth = std::max<int64_t>((n - head) / 8, 1);
+                CHECK_HIP(hipMemcpyAsync(&pinned[6], F->fptr + head, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+                CHECK_HIP(hipMemcpyAsync(&pinned[7], F->fptr + head + eighth, sizeof(int64_t),
+                                         hipMemcpyDeviceToHost, s));
+                CHECK_HIP(hipStreamSynchronize(s));
+                chain_len = (double)(pinned[7] - pinned[6]) / (double)eighth;
+            }
+            F->chain_lanes = chain_len <= LANES16_LEN ? 16 : chain_len <= LANES32_LEN ? 32 : 64;
+            if (random && !large) {
+                F->chain_per_cu = ALL_PER_CU;
+            } else if (random && chain_len > LANES16_LEN) {
                 status = chain_build(F, head, CHAIN_PLAN_ROWS, keep, pinned, s);
                 if (status) goto done;
+                const int64_t m = F->chain.m > 0 ? F->chain.m : chain_rows(n);
+                if (F->chain.m > 0 || n - (head + m) >= WIDE_MIN_ROWS) F->chain_end = head + m;
+                F->chain_per_cu = F->chain_end < n || F->chain.m > 0 ? CHAIN_PER_CU : ALL_PER_CU;
             }
-            const int64_t m = F->chain.m > 0 ? F->chain.m : chain_rows(n);
-            if (F->chain.m > 0 || n - (head + m) >= WIDE_MIN_ROWS) F->chain_end = head + m;
-            F->chain_per_cu = F->chain_end < n || F->chain.m > 0 ? CHAIN_PER_CU : ALL_PER_CU;
         }
         if (head > 0) {
             const size_t hb = (size_t)(head * (head + 1) / 2) * vbytes;

@@ -65,7 +65,8 @@ struct srw_factor {
     // substituted by a launch of their own (n: one launch for all)
     int64_t chain_end = 0;
     int32_t chain_per_cu = 0;  // workgroups per CU of that launch, at most, a wave per row
-                               // (0: as many as fit, lanes by row length)
+                               // (0: as many as fit, chain_lanes lanes per row)
+    int32_t chain_lanes = 64;  // 16, 32 or 64
     ChainPlan chain;
     void* hx = nullptr;
     void* hxt = nullptr;

@@ -774,23 +774,26 @@ hipError_t coop_launch(K kernel, int64_t rows, void** args, hipStream_t s, int p
                                       args, 0, s);
 }
 
-// Lanes per row past the chain, by the factor's mean row length (a lane takes two entries
-// at once): 16 lanes up to 28 entries, 32 up to 56, a wave past them.
+// As many workgroups as fit, lanes per row.
 template <typename T, bool FWD>
-hipError_t trsv_launch(const srw_factor* F, int64_t rows, void** args, hipStream_t s)
+hipError_t trsv_launch(int lanes, int64_t rows, void** args, hipStream_t s)
 {
-    if (F->nnz_y > 56 * F->n) return coop_launch(k_trsv<T, FWD, 64, false>, rows, args, s);
-    if (F->nnz_y > 28 * F->n) return coop_launch(k_trsv<T, FWD, 32, false>, (rows + 1) / 2, args, s);
+    if (lanes == 64) return coop_launch(k_trsv<T, FWD, 64, false>, rows, args, s);
+    if (lanes == 32) return coop_launch(k_trsv<T, FWD, 32, false>, (rows + 1) / 2, args, s);
     return coop_launch(k_trsv<T, FWD, 16, false>, (rows + 3) / 4, args, s);
 }
 
+// Lanes per row past the chain, by the factor's mean row length (a lane takes two entries
+// at once): 16 lanes up to 28 entries, 32 up to 56, a wave past them.
+int wide_lanes(const srw_factor* F) { return F->nnz_y > 56 * F->n ? 64 : F->nnz_y > 28 * F->n ? 32 : 16; }
+
 int fill_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(grid_for(n, BLOCK), 1), 2048); }
 
-// The substitution over slots h..n-1 of one triangle of the plan.  In random order in two
-// launches: the slots before chain_end hold most of the dependency chain, the others most of
-// the work.  In given and natural orders the chain runs through all rows, in one launch with
-// lanes by row length: a wave per row, as for the chain, takes longer here, and longer than in
-// a kernel for waves per row alone (IC(0) in natural order, one application, in us, that
+// The substitution over slots h..n-1 of one triangle of the plan.  In random order with long
+// chain rows in two launches: the slots before chain_end hold most of the dependency chain,
+// the others most of the work.  Else in one launch.  In given and natural orders, whose chain
+// runs through all rows, a wave per row takes longer here than in a kernel for waves per row
+// alone, and lanes by row length less (IC(0) in natural order, one application, in us, that
 // kernel / a wave per row / by row length: 2D grid 300^2 2,047 / 2,343 / 1,509, Laplace 50^3
 // 2,279 / 2,598 / 825, 64^3 1,850 / 2,010 / 1,010; the walks' factors in natural order: 2D
 // grid 300^2 20,936 / 23,340 / 16,655, asymmetric 40^3 2,705 / 2,998 / 1,933).
@@ -818,7 +821,7 @@ hipError_t substitute(const srw_factor* F, int64_t h, const double* rhs, const T
         else if (chain && F->chain_per_cu > 0)
             e = coop_launch(k_trsv<T, FWD, 64, false>, hi - lo, args, s, F->chain_per_cu);
         else
-            e = trsv_launch<T, FWD>(F, hi - lo, args, s);
+            e = trsv_launch<T, FWD>(chain ? F->chain_lanes : wide_lanes(F), hi - lo, args, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -121,3 +121,18 @@ def test_two_games_in_given_orders(srw, order):  # noqa: F811
         _, rx, _, _ = O.bicgstab(A, ref, b, 0.0, k)
         assert np.linalg.norm(np_(x) - rx) <= 1e-10 * np.linalg.norm(rx)
     F.free()
+
+
+@pytest.mark.parametrize("walks", [64, 256])
+def test_two_games_on_either_side_of_the_plan(srw, walks):  # noqa: F811
+    """Chain rows of 8.8 entries (one launch) and of 18.7 (the plan): the oracle's iterates."""
+    A = W.grid_asym((53, 51, 52), ground_frac=0.0005, seed=3)
+    ref = O.build_factor_ldu(A, walks, 1e-3, 7, threads=8)
+    M = srw.Matrix.from_host(A, DEV)
+    b = W.rhs(A.n, seed=5)
+    F = srw.build_factor_ldu(M, walks, 1e-3, 7)
+    for k in (1, 2):
+        _, x, _, _ = srw.bicgstab_solve(M, F, torch.as_tensor(b, device=DEV), 0.0, k)
+        _, rx, _, _ = O.bicgstab(A, ref, b, 0.0, k)
+        assert np.linalg.norm(np_(x) - rx) <= 1e-10 * np.linalg.norm(rx)
+    F.free()
