@@ -2188,7 +2188,8 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
             // 32 walks: 605 us an application, 694 by mean row length)
             F->chain_per_cu = 64;
         } else if (n > head) {
-            const bool random = (opt.ordering == SRW_ORDER_RANDOM || random_rank) && !ic0 && opt.head_rows >= 0;
+            const bool random = (opt.ordering == SRW_ORDER_RANDOM || random_rank) && !ic0;
+            const bool headless = opt.head_rows < 0;  // (then without a plan too)
             const bool large = n - head >= CHAIN_PLAN_ROWS;
             double chain_len = 0.0;  // mean length of the first eighth of the rows past the head
             if (!random || large) {
@@ -2200,7 +2201,9 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
                 chain_len = (double)(pinned[7] - pinned[6]) / (double)eighth;
             }
             F->chain_lanes = chain_len <= LANES16_LEN ? 16 : chain_len <= LANES32_LEN ? 32 : 64;
-            if (random && !large) {
+            if (random && headless && (!large || chain_len > LANES16_LEN)) {
+                F->chain_per_cu = 64;
+            } else if (random && !large) {
                 F->chain_per_cu = ALL_PER_CU;
             } else if (random && chain_len > LANES16_LEN) {
                 status = chain_build(F, head, CHAIN_PLAN_ROWS, keep, pinned, s);
