@@ -66,92 +66,125 @@ __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c)
 }
 
 // ------------------------------------------------------------------- features
-// e_k / a_k of every node.
 static_assert(NF == 8, "k_features writes a row as two float4");
-constexpr int FEAT_TILE = 1024;  // entries of 256 rows in LDS at once
+constexpr int FEAT_TILE = 1024;  // entries in LDS at once
 
-// Rows per workgroup: 256; their entries come into LDS in entry order (a thread that reads
-// its own row touches a cache line per entry and array), where each thread then goes
-// through its row's, first entry first.  128^3 grid: 64 -> 36 us (the ratios), 128 -> 88 us
-// (the features, their rows written as two float4); the entries take 40 us at the rate of a
-// copy.
-__global__ __launch_bounds__(256) void k_excess_ratio(int64_t n, const int64_t* __restrict__ rowptr,
+// Rows at a time of a workgroup of 256 threads.  Up to 128 entries a row on average their
+// entries come into LDS in entry order (a thread that reads its own row touches a cache line
+// per entry and array), where each thread then goes through its row's, first entry first.
+// 128^3 grid, 256 rows: 64 -> 36 us (the ratios), 128 -> 88 us (the features, their rows
+// written as two float4); the entries take 40 us at the rate of a copy.  The longer the rows,
+// the fewer of them a tile holds, so a workgroup takes fewer (both kernels, in us, a thread
+// per row in memory / 256 / 64 / 16 rows: 300,000 rows of 13 entries 226 / 83 / 78 / 115, 41
+// entries - / 242 / 214 / 230, 101 entries 2,098 / 935 / 809 / 766; 3,000 rows of 66 entries 80
+// / 339 / 112 / 57).  Past 128 entries few rows fit a tile, and a thread per row reads it from
+// memory where there are at most 65,536 rows (30,000 rows of 398 entries 579 us, 1,269 with 16
+// rows in tiles, 1,032 at best; but 300,000 rows of 201 entries 4,105 and 2,360), past 320
+// everywhere (300,000 rows of 400 entries 8,060 and 8,820 us).
+struct FeatPlan {
+    int rows;    // of a workgroup at once
+    bool tiles;  // entries through LDS
+};
+
+FeatPlan feat_plan(int64_t n, int64_t nnz)
+{
+    if (nnz > 320 * n || (nnz > 128 * n && n <= 65536)) return {256, false};
+    return {nnz <= 12 * n ? 256 : nnz <= 48 * n ? 64 : 16, true};
+}
+
+// f(column, value, place) for the entries of the thread's row [r0, r1), in entry order;
+// load(place in the tile, column) when an entry comes into LDS.
+template <bool TILES, typename L, typename F>
+__device__ __forceinline__ void row_entries(int64_t e0, int64_t e1, int64_t r0, int64_t r1,
+                                            const int32_t* __restrict__ col,
+                                            const double* __restrict__ val, int32_t* tc, double* tv,
+                                            L load, F f)
+{
+    if (!TILES) {
+        for (int64_t q = r0; q < r1; ++q) f(col[q], val[q], -1);
+        return;
+    }
+    for (int64_t t0 = e0; t0 < e1; t0 += FEAT_TILE) {
+        const int m = (int)(e1 - t0 < FEAT_TILE ? e1 - t0 : FEAT_TILE);
+#pragma unroll
+        for (int q = 0; q < FEAT_TILE; q += 256) {
+            const int at = q + (int)threadIdx.x;
+            if (at < m) {
+                const int32_t j = col[t0 + at];
+                tc[at] = j;
+                tv[at] = val[t0 + at];
+                load(at, j);
+            }
+        }
+        __syncthreads();
+        const int64_t lo = r0 > t0 ? r0 : t0, hi = r1 < t0 + m ? r1 : t0 + m;
+        for (int64_t e = lo; e < hi; ++e) f(tc[e - t0], tv[e - t0], (int)(e - t0));
+        __syncthreads();
+    }
+}
+
+// e_k / a_k of every node.
+template <bool TILES>
+__global__ __launch_bounds__(256) void k_excess_ratio(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ col,
                                                       const double* __restrict__ val,
                                                       double* __restrict__ ratio)
 {
-    __shared__ int32_t tc[FEAT_TILE];
-    __shared__ double tv[FEAT_TILE];
-    const int64_t base = (int64_t)blockIdx.x * 256, k = base + threadIdx.x;
-    const int64_t r0 = k < n ? rowptr[k] : 0, r1 = k < n ? rowptr[k + 1] : 0;
-    const int64_t e0 = rowptr[base], e1 = rowptr[base + 256 < n ? base + 256 : n];
+    __shared__ int32_t tc[TILES ? FEAT_TILE : 1];
+    __shared__ double tv[TILES ? FEAT_TILE : 1];
+    const int64_t base = (int64_t)blockIdx.x * rows, k = base + threadIdx.x;
+    const bool mine = (int)threadIdx.x < rows && k < n;
+    const int64_t r0 = mine ? rowptr[k] : 0, r1 = mine ? rowptr[k + 1] : 0;
     double a = 0.0, s = 0.0;
-    for (int64_t t0 = e0; t0 < e1; t0 += FEAT_TILE) {
-        const int m = (int)(e1 - t0 < FEAT_TILE ? e1 - t0 : FEAT_TILE);
-#pragma unroll
-        for (int q = 0; q < FEAT_TILE; q += 256)
-            if (q + (int)threadIdx.x < m) {
-                tc[q + threadIdx.x] = col[t0 + q + threadIdx.x];
-                tv[q + threadIdx.x] = val[t0 + q + threadIdx.x];
-            }
-        __syncthreads();
-        const int64_t lo = r0 > t0 ? r0 : t0, hi = r1 < t0 + m ? r1 : t0 + m;
-        for (int64_t q = lo; q < hi; ++q) {
-            if (tc[q - t0] == k) a = tv[q - t0];
-            else s = s + (-tv[q - t0]);
-        }
-        __syncthreads();
-    }
-    if (k < n) ratio[k] = (a - s) / a;
+    row_entries<TILES>(rowptr[base], rowptr[base + rows < n ? base + rows : n], r0, r1, col, val, tc, tv,
+                       [](int, int32_t) {},
+                       [&](int32_t j, double v, int) {
+                           if (j == k) a = v;
+                           else s = s + (-v);
+                       });
+    if (mine) ratio[k] = (a - s) / a;
 }
 
-__global__ __launch_bounds__(256) void k_features(int64_t n, const int64_t* __restrict__ rowptr,
+// The eight features of a row (float64 arithmetic, stored as float32), in order:
+// degree, log a_k, e_k / a_k, tau_k, fraction of neighbours ranked above k,
+// log(max w / min w), log(n / (rank_k + 1)), mean of e_j / a_j over neighbours j.
+template <bool TILES>
+__global__ __launch_bounds__(256) void k_features(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                   const int32_t* __restrict__ col,
                                                   const double* __restrict__ val,
                                                   const int32_t* __restrict__ rank,
                                                   const double* __restrict__ ratio,
                                                   float* __restrict__ feat)
 {
-    __shared__ int32_t tc[FEAT_TILE], tr[FEAT_TILE];
-    __shared__ double tv[FEAT_TILE], tx[FEAT_TILE];
-    const int64_t base = (int64_t)blockIdx.x * 256, k = base + threadIdx.x;
-    const int64_t r0 = k < n ? rowptr[k] : 0, r1 = k < n ? rowptr[k + 1] : 0;
-    const int64_t e0 = rowptr[base], e1 = rowptr[base + 256 < n ? base + 256 : n];
-    const int32_t rk = k < n ? rank[k] : 0;
+    __shared__ int32_t tc[TILES ? FEAT_TILE : 1], tr[TILES ? FEAT_TILE : 1];
+    __shared__ double tv[TILES ? FEAT_TILE : 1], tx[TILES ? FEAT_TILE : 1];
+    const int64_t base = (int64_t)blockIdx.x * rows, k = base + threadIdx.x;
+    const bool mine = (int)threadIdx.x < rows && k < n;
+    const int64_t r0 = mine ? rowptr[k] : 0, r1 = mine ? rowptr[k + 1] : 0;
+    const int32_t rk = mine ? rank[k] : 0;
     double a = 0.0, motel = 0.0, wmin = 0.0, wmax = 0.0, rsum = 0.0;
     int deg = 0, higher = 0;
-    for (int64_t t0 = e0; t0 < e1; t0 += FEAT_TILE) {
-        const int m = (int)(e1 - t0 < FEAT_TILE ? e1 - t0 : FEAT_TILE);
-#pragma unroll
-        for (int q = 0; q < FEAT_TILE; q += 256)
-            if (q + (int)threadIdx.x < m) {
-                const int32_t j = col[t0 + q + threadIdx.x];
-                tc[q + threadIdx.x] = j;
-                tv[q + threadIdx.x] = val[t0 + q + threadIdx.x];
-                tr[q + threadIdx.x] = rank[j];
-                tx[q + threadIdx.x] = ratio[j];
-            }
-        __syncthreads();
-        const int64_t lo = r0 > t0 ? r0 : t0, hi = r1 < t0 + m ? r1 : t0 + m;
-        for (int64_t e = lo; e < hi; ++e) {
-            const int q = (int)(e - t0);
-            if (tc[q] == k) {
-                a = tv[q];
-                continue;
-            }
-            const double w = -tv[q];
-            if (deg == 0 || w < wmin) wmin = w;
-            if (deg == 0 || w > wmax) wmax = w;
-            ++deg;
-            if (tr[q] > rk) {
-                ++higher;
-                motel = motel + w;
-            }
-            rsum = rsum + tx[q];
-        }
-        __syncthreads();
-    }
-    if (k >= n) return;
+    row_entries<TILES>(rowptr[base], rowptr[base + rows < n ? base + rows : n], r0, r1, col, val, tc, tv,
+                       [&](int at, int32_t j) {
+                           tr[at] = rank[j];
+                           tx[at] = ratio[j];
+                       },
+                       [&](int32_t j, double v, int at) {
+                           if (j == k) {
+                               a = v;
+                               return;
+                           }
+                           const double w = -v;
+                           if (deg == 0 || w < wmin) wmin = w;
+                           if (deg == 0 || w > wmax) wmax = w;
+                           ++deg;
+                           if ((TILES ? tr[at] : rank[j]) > rk) {
+                               ++higher;
+                               motel = motel + w;
+                           }
+                           rsum = rsum + (TILES ? tx[at] : ratio[j]);
+                       });
+    if (!mine) return;
     float f[NF];
     f[0] = (float)deg;
     f[1] = (float)log(a);
@@ -541,9 +574,15 @@ int features_impl(const srw_csr* A, const int32_t* rank, float* feat, hipStream_
     if (n == 0) return SRW_OK;
     double* ratio = nullptr;
     SRW_HIP(dev_alloc((void**)&ratio, n * sizeof(double)));
-    const int g = grid_for(n, BLOCK);
-    k_excess_ratio<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, ratio);
-    k_features<<<g, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, rank, ratio, feat);
+    const FeatPlan P = feat_plan(n, A->nnz);
+    const int g = (int)((n + P.rows - 1) / P.rows);
+    if (P.tiles) {
+        k_excess_ratio<true><<<g, BLOCK, 0, s>>>(n, P.rows, A->rowptr, A->col, A->val, ratio);
+        k_features<true><<<g, BLOCK, 0, s>>>(n, P.rows, A->rowptr, A->col, A->val, rank, ratio, feat);
+    } else {
+        k_excess_ratio<false><<<g, BLOCK, 0, s>>>(n, P.rows, A->rowptr, A->col, A->val, ratio);
+        k_features<false><<<g, BLOCK, 0, s>>>(n, P.rows, A->rowptr, A->col, A->val, rank, ratio, feat);
+    }
     hipError_t e = hipGetLastError();
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;

@@ -147,8 +147,8 @@ __device__ __forceinline__ uint32_t threshold32(double c, double d)
     return (uint32_t)x;
 }
 
-// Row i of a CSR matrix times x, for the workgroup's 256 consecutive rows at `base` (thread
-// t: row base + t; all threads call it).  The products are made in entry order, 2,048 at a
+// Row i of a CSR matrix times x, for `rows` (at most 256) consecutive rows at `base` (thread
+// t < rows: row base + t; all threads of the workgroup call it).  The products are made in entry order, 2,048 at a
 // time, by consecutive threads, and each thread then adds its row's from LDS, first entry
 // first, as a loop over the row would: the same sums.  A thread that reads its own row
 // alone touches a cache line per entry: on 2M rows at degree 24 (51M entries) 2,210 us
@@ -156,15 +156,23 @@ __device__ __forceinline__ uint32_t threshold32(double c, double d)
 // the rate of a copy, the gathers of x the rest); 70 us either way on the grid 128^3.
 constexpr int ROWS_TILE = 2048;
 
-__device__ __forceinline__ double row_times(int64_t base, int64_t n, const int64_t* __restrict__ rowptr,
+// Rows a workgroup takes at once.  A tile holds few long rows, so a workgroup with many of them
+// goes through many tiles with few threads at work (ten steps of BiCGSTAB without a
+// preconditioner, in us, a thread per row in memory / 256 rows / this rule: 3,000 rows of 49
+// entries 1,557 / 1,634 / 1,221, of 101 entries 1,973 / 2,699 / 1,535, of 376 entries 4,093 /
+// 16,675 / 2,111; 300,000 rows of 101 entries 26,407 / 8,218 / 6,817).
+inline int rows_at_once(int64_t n, int64_t nnz) { return nnz <= 32 * n ? 256 : nnz <= 128 * n ? 64 : 16; }
+
+__device__ __forceinline__ double row_times(int64_t base, int rows, int64_t n, const int64_t* __restrict__ rowptr,
                                             const int32_t* __restrict__ col,
                                             const double* __restrict__ val,
                                             const double* __restrict__ x, double* prod)
 {
     const int tid = threadIdx.x;
     const int64_t i = base + tid;
-    const int64_t r0 = i < n ? rowptr[i] : 0, r1 = i < n ? rowptr[i + 1] : 0;
-    const int64_t e0 = rowptr[base], e1 = rowptr[base + 256 < n ? base + 256 : n];
+    const bool mine = tid < rows && i < n;
+    const int64_t r0 = mine ? rowptr[i] : 0, r1 = mine ? rowptr[i + 1] : 0;
+    const int64_t e0 = rowptr[base], e1 = rowptr[base + rows < n ? base + rows : n];
     double acc = 0.0;
     for (int64_t t0 = e0; t0 < e1; t0 += ROWS_TILE) {
         const int m = (int)(e1 - t0 < ROWS_TILE ? e1 - t0 : ROWS_TILE);

@@ -85,15 +85,15 @@ __device__ __forceinline__ double block_sum(double v, double* lds)
     for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < (n); i += (int64_t)gridDim.x * BLOCK)
 
 // y = A x
-__global__ __launch_bounds__(BLOCK) void k_spmv(int64_t n, const int64_t* __restrict__ rowptr,
+__global__ __launch_bounds__(BLOCK) void k_spmv(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                 const int32_t* __restrict__ col,
                                                 const double* __restrict__ val,
                                                 const double* __restrict__ x, double* __restrict__ y)
 {
     __shared__ double prod[ROWS_TILE];
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
-        const double acc = row_times(base, n, rowptr, col, val, x, prod);
-        if (base + threadIdx.x < n) y[base + threadIdx.x] = acc;
+    for (int64_t base = (int64_t)blockIdx.x * rows; base < n; base += (int64_t)gridDim.x * rows) {
+        const double acc = row_times(base, rows, n, rowptr, col, val, x, prod);
+        if ((int)threadIdx.x < rows && base + threadIdx.x < n) y[base + threadIdx.x] = acc;
     }
 }
 
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(BLOCK) void k_bicg_xr(int64_t n, double* __restrict
 }
 
 // r = b - A x, partials of r . r
-__global__ __launch_bounds__(BLOCK) void k_bicg_residual(int64_t n, const int64_t* __restrict__ rowptr,
+__global__ __launch_bounds__(BLOCK) void k_bicg_residual(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                          const int32_t* __restrict__ col,
                                                          const double* __restrict__ val,
                                                          const double* __restrict__ x,
@@ -200,10 +200,10 @@ __global__ __launch_bounds__(BLOCK) void k_bicg_residual(int64_t n, const int64_
     __shared__ double lds[BLOCK / 64];
     __shared__ double prod[ROWS_TILE];
     double acc = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
-        const double q = row_times(base, n, rowptr, col, val, x, prod);
+    for (int64_t base = (int64_t)blockIdx.x * rows; base < n; base += (int64_t)gridDim.x * rows) {
+        const double q = row_times(base, rows, n, rowptr, col, val, x, prod);
         const int64_t i = base + threadIdx.x;
-        if (i < n) {
+        if ((int)threadIdx.x < rows && i < n) {
             const double ri = b[i] - q;
             r[i] = ri;
             acc += ri * ri;
@@ -304,6 +304,8 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
 {
     const int64_t n = A->n;
     const int rg = (int)std::max<int64_t>(1, std::min<int64_t>((n + BLOCK - 1) / BLOCK, RED));
+    const int rows = rows_at_once(n, A->nnz);  // of the products with A
+    const int mg = (int)std::max<int64_t>(1, std::min<int64_t>((n + rows - 1) / rows, RED));
     const size_t vec = (size_t)std::max<int64_t>(n, 1);
     double* ws = nullptr;
     // r, rt, p, v, ph, s, sh, t, preconditioner scratch, partials, sums, err
@@ -326,8 +328,8 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
     int32_t it = 0;
     double rel = 0.0;
     // sum the partials (one or two dots) and bring them to the host
-    auto reduce = [&](int two, double* o) -> hipError_t {
-        k_sums<<<1, BLOCK, 0, s>>>(part, rg, two, sums);
+    auto reduce = [&](int np, int two, double* o) -> hipError_t {
+        k_sums<<<1, BLOCK, 0, s>>>(part, np, two, sums);
         hipError_t ee = hipGetLastError();
         if (ee == hipSuccess)
             ee = hipMemcpyAsync(host, sums, 2 * sizeof(double), hipMemcpyDeviceToHost, s);
@@ -340,7 +342,7 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
                     double* o) -> hipError_t {
         k_dots<<<rg, BLOCK, 0, s>>>(n, a1, b1, c1, d1, part);
         hipError_t ee = hipGetLastError();
-        return ee == hipSuccess ? reduce(c1 ? 1 : 0, o) : ee;
+        return ee == hipSuccess ? reduce(rg, c1 ? 1 : 0, o) : ee;
     };
     auto precond = [&](const double* src, double* dst) -> hipError_t {
         if (!F) {
@@ -384,7 +386,7 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
             STEP((k_bicg_p<<<rg, BLOCK, 0, s>>>(n, r, v, p, beta, omega, first ? 1 : 0)));
             first = false;
             STEP(e = precond(p, ph));
-            STEP((k_spmv<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, ph, v)));
+            STEP((k_spmv<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, ph, v)));
             ++it;
             STEP(e = dots(rt, v, nullptr, nullptr, o));
             if (F && solve_failed()) {
@@ -396,28 +398,28 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
             if (rtv == 0.0) break;
             alpha = rho / rtv;
             STEP((k_bicg_s<<<rg, BLOCK, 0, s>>>(n, r, v, alpha, sv, part)));
-            STEP(e = reduce(0, o));
+            STEP(e = reduce(rg, 0, o));
             bool converged = false;
             if (std::sqrt(o[0]) <= tol * bnorm) {
                 STEP((k_bicg_half<<<rg, BLOCK, 0, s>>>(n, x, ph, alpha)));
                 converged = true;
             } else {
                 STEP(e = precond(sv, sh));
-                STEP((k_spmv<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, sh, t)));
+                STEP((k_spmv<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, sh, t)));
                 STEP(e = dots(t, t, t, sv, o));
                 const double tt = o[0], ts = o[1];
                 if (tt == 0.0) break;
                 omega = ts / tt;
                 STEP((k_bicg_xr<<<rg, BLOCK, 0, s>>>(n, x, r, ph, sh, sv, t, alpha, omega, part)));
-                STEP(e = reduce(0, o));
+                STEP(e = reduce(rg, 0, o));
                 rho_prev = rho;
                 if (!std::isfinite(o[0])) break;
                 if (std::sqrt(o[0]) <= tol * bnorm) converged = true;
                 else if (omega == 0.0) break;
             }
             if (converged) {
-                STEP((k_bicg_residual<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, x, b, r, part)));
-                STEP(e = reduce(0, o));
+                STEP((k_bicg_residual<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, x, b, r, part)));
+                STEP(e = reduce(mg, 0, o));
                 if (std::sqrt(o[0]) <= tol * bnorm) {
                     status = SRW_OK;
                     break;
@@ -428,8 +430,8 @@ int bicgstab_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, 
             }
         }
         // true relative residual of the returned iterate
-        STEP((k_bicg_residual<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, x, b, r, part)));
-        STEP(e = reduce(0, o));
+        STEP((k_bicg_residual<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, x, b, r, part)));
+        STEP(e = reduce(mg, 0, o));
         rel = std::sqrt(o[0]) / bnorm;
         if (F && solve_failed()) {
             gave_up = true;

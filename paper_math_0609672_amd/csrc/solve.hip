@@ -73,7 +73,7 @@ __global__ __launch_bounds__(BLOCK) void k_finalize(const double* __restrict__ p
 }
 
 // q = A p (every row's entries added in CSR order) and partials of p . q
-__global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, const int64_t* __restrict__ rowptr,
+__global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                     const int32_t* __restrict__ col,
                                                     const double* __restrict__ val,
                                                     const double* __restrict__ p,
@@ -82,10 +82,10 @@ __global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, const int64_t* __
     __shared__ double lds[BLOCK / 64];
     __shared__ double prod[ROWS_TILE];
     double s = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
-        const double acc = row_times(base, n, rowptr, col, val, p, prod);
+    for (int64_t base = (int64_t)blockIdx.x * rows; base < n; base += (int64_t)gridDim.x * rows) {
+        const double acc = row_times(base, rows, n, rowptr, col, val, p, prod);
         const int64_t i = base + threadIdx.x;
-        if (i < n) {
+        if ((int)threadIdx.x < rows && i < n) {
             q[i] = acc;
             s += p[i] * acc;
         }
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmv_dot(int64_t n, const int64_t* __
 }
 
 // r = b - A x and partials of r . r
-__global__ __launch_bounds__(BLOCK) void k_residual(int64_t n, const int64_t* __restrict__ rowptr,
+__global__ __launch_bounds__(BLOCK) void k_residual(int64_t n, int rows, const int64_t* __restrict__ rowptr,
                                                     const int32_t* __restrict__ col,
                                                     const double* __restrict__ val,
                                                     const double* __restrict__ x,
@@ -105,10 +105,10 @@ __global__ __launch_bounds__(BLOCK) void k_residual(int64_t n, const int64_t* __
     __shared__ double lds[BLOCK / 64];
     __shared__ double prod[ROWS_TILE];
     double s = 0.0;
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < n; base += (int64_t)gridDim.x * BLOCK) {
-        const double acc = row_times(base, n, rowptr, col, val, x, prod);
+    for (int64_t base = (int64_t)blockIdx.x * rows; base < n; base += (int64_t)gridDim.x * rows) {
+        const double acc = row_times(base, rows, n, rowptr, col, val, x, prod);
         const int64_t i = base + threadIdx.x;
-        if (i < n) {
+        if ((int)threadIdx.x < rows && i < n) {
             const double ri = b[i] - acc;
             r[i] = ri;
             s += ri * ri;
@@ -896,9 +896,9 @@ hipError_t apply_any(const srw_factor* F, const double* r, void* work, double* z
                                     : apply_plan<double>(F, r, (double*)work, z, err, s);
 }
 
-int red_grid(int64_t n)
+int red_grid(int64_t n, int rows = BLOCK)
 {
-    const int64_t g = (n + BLOCK - 1) / BLOCK;
+    const int64_t g = (n + rows - 1) / rows;
     return (int)std::max<int64_t>(1, std::min<int64_t>(g, RED_GRID));
 }
 
@@ -1110,6 +1110,7 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
 {
     const int64_t n = A->n;
     const int rg = red_grid(n);
+    const int rows = rows_at_once(n, A->nnz), mg = red_grid(n, rows);  // of the products with A
     const int eg = rg;  // elementwise kernels share the fixed grid
     double* ws = nullptr;
     double* host = nullptr;
@@ -1170,8 +1171,8 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
         STEP((k_dot<<<rg, BLOCK, 0, s>>>(n, r, z, partials)));
         STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, rg, sc, OP_RHO0)));
         while (it < max_iter) {
-            STEP((k_spmv_dot<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, p, q, partials)));
-            STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, rg, sc, OP_ALPHA)));
+            STEP((k_spmv_dot<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, p, q, partials)));
+            STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, mg, sc, OP_ALPHA)));
             STEP((k_update_xr<<<rg, BLOCK, 0, s>>>(n, x, r, p, q, sc, partials)));
             STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, rg, sc, OP_RR)));
             ++it;
@@ -1183,8 +1184,8 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
                 goto out;
             }
             if (std::sqrt(rr) <= tol * bnorm) {
-                STEP((k_residual<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, x, b, r, partials)));
-                STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, rg, sc, OP_RR)));
+                STEP((k_residual<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, x, b, r, partials)));
+                STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, mg, sc, OP_RR)));
                 if ((e = read_scalar(S_RR, &rr)) != hipSuccess) goto out;
                 if (std::sqrt(rr) <= tol * bnorm) {
                     status = SRW_OK;
@@ -1203,8 +1204,8 @@ int pcg_impl(const srw_csr* A, srw_factor* F, const double* b, double tol, int32
             STEP((k_update_p<<<eg, BLOCK, 0, s>>>(n, z, p, sc)));
         }
         // true relative residual of the returned iterate
-        STEP((k_residual<<<rg, BLOCK, 0, s>>>(n, A->rowptr, A->col, A->val, x, b, r, partials)));
-        STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, rg, sc, OP_RR)));
+        STEP((k_residual<<<mg, BLOCK, 0, s>>>(n, rows, A->rowptr, A->col, A->val, x, b, r, partials)));
+        STEP((k_finalize<<<1, BLOCK, 0, s>>>(partials, mg, sc, OP_RR)));
         double rr = 0.0;
         if ((e = read_scalar(S_RR, &rr)) != hipSuccess) goto out;
         rel = std::sqrt(rr) / bnorm;

@@ -7,8 +7,9 @@ import pytest
 
 import oracle as O
 from oracle import budget as B
+from paper_math_0609672_amd import workloads as W
 from test_gpu_parity import DEV, np_, srw, torch  # noqa: F401
-from test_gpu_row_products import CASES
+from test_gpu_row_products import CASES, DENSE
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +29,13 @@ def test_features_match_oracle(srw, name):  # noqa: F811
     assert st == 0
     for f in (np_(srw.row_features(M, rank)), np_(odd).reshape(A.n, 8)):
         assert np.all(np.abs(f - ref) <= np.spacing(np.abs(ref)))
+
+
+# mean row lengths past 12, 48 and 128 entries: 64 and 16 rows to a workgroup, a thread per row
+@pytest.mark.parametrize("name", ["middle_rows"] + list(DENSE))
+def test_features_of_dense_rows_match_oracle(srw, name):  # noqa: F811
+    A = DENSE[name] if name in DENSE else W.random_graph(1003, 10000, seed=5, ground_frac=0.2)
+    M = srw.Matrix.from_host(A, DEV)
+    f = np_(srw.row_features(M, srw.ordering(A.n, 11, DEV)))
+    ref = B.features(A, O.rank(A.n, 11)).astype(np.float32)
+    assert np.all(np.abs(f - ref) <= np.spacing(np.abs(ref)))

@@ -48,3 +48,39 @@ def test_iterates_match_oracle(srw, name):  # noqa: F811
     _, x, _, _ = srw.bicgstab_solve(M, None, bt, 0.0, 1)
     _, rx, _, _ = O.bicgstab(A, None, b, 0.0, 1)
     assert np.abs(np_(x) - rx).max() <= 1e-10 * np.abs(rx).max()
+
+
+# mean row lengths past 32 and past 128 entries: 64 and 16 rows to a workgroup
+DENSE = {
+    "64_rows_at_once": W.random_graph(1003, 24000, seed=5, ground_frac=0.2),
+    "16_rows_at_once": W.random_graph(515, 40000, seed=6, ground_frac=0.2),
+    "partial_last_group": W.random_graph(130, 8300, seed=7, ground_frac=0.2),
+}
+
+
+@pytest.mark.parametrize("name", list(DENSE))
+def test_iterates_of_dense_rows_match_oracle(srw, name):  # noqa: F811
+    """The bound of the test above."""
+    A = DENSE[name]
+    M = srw.Matrix.from_host(A, DEV)
+    F, ref = srw.build_factor(M, 8, 0.0, 5), O.build_factor(A, 8, 0.0, 5)
+    b = np.random.default_rng(1).standard_normal(A.n)
+    bt = torch.as_tensor(b, device=DEV)
+    for k in (1, 3):
+        _, x, _, rel = srw.pcg_solve(M, F, bt, 0.0, k)
+        _, rx, _, rrel = O.pcg(A, ref, b, 0.0, k)
+        assert np.abs(np_(x) - rx).max() <= 1e-10 * np.abs(rx).max()
+        assert abs(rel - rrel) <= 1e-10 * rrel
+        _, x, _, _ = srw.bicgstab_solve(M, None, bt, 0.0, k)
+        _, rx, _, _ = O.bicgstab(A, None, b, 0.0, k)
+        assert np.abs(np_(x) - rx).max() <= 1e-10 * np.abs(rx).max()
+
+
+@pytest.mark.parametrize("name", ["255", "256", "257"])
+def test_third_bicgstab_iterate_matches_oracle(srw, name):  # noqa: F811
+    """Where one ulp of b changes the oracle's own third iterate by less than 1e-12."""
+    A = CASES[name]
+    b = np.random.default_rng(1).standard_normal(A.n)
+    _, x, _, _ = srw.bicgstab_solve(srw.Matrix.from_host(A, DEV), None, torch.as_tensor(b, device=DEV), 0.0, 3)
+    _, rx, _, _ = O.bicgstab(A, None, b, 0.0, 3)
+    assert np.abs(np_(x) - rx).max() <= 1e-10 * np.abs(rx).max()
