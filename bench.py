@@ -12,9 +12,10 @@ per row, drop tolerance 1e-4, FP64 factor, one right-hand side N(0, 1), PCG to
 ||b - Ax|| <= 1e-8 ||b||; seed 0.
 
 Prints one JSON line (rank 0).  `roofline` is for the walk kernel, the dominant
-kernel: algorithmic bytes = 12 B per step + 8 B per entry of the row the step
-leaves (counted exactly by the kernel) over the kernel's HIP-event duration on the
-build stream.  `cpu_baseline` times the CPU oracle on the whole workload (build and
+kernel: its measured HBM traffic (profiles/k_walk_traffic.json, where it was taken on the
+present kernel) over its HIP-event duration on the build stream, and beside it the effective
+rate of its algorithmic bytes = 12 B per step + 8 B per entry of the row the step leaves
+(counted exactly by the kernel).  `cpu_baseline` times the CPU oracle on the whole workload (build and
 solve), its rows' walks and tallies split over the host threads.
 """
 import argparse
@@ -307,22 +308,9 @@ def run_batch(args):
         "factor_C": C,
         "C_over_N": round(C / N, 3),
         "phase_ms": {k: round(sum(r["stats"]["phase_ms"][k] for r in runs) / K, 3) for k in srw.PHASES},
-        "roofline": {
-            "kernel": "k_walk",
-            "bound": "hbm",
-            "achieved": round(achieved, 1),
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic(args.workload, args.precision, s0["walk_waves"]),
-            "alg_bytes_per_launch": walk_bytes,
-            "avg_launch_ms": round(walk_ms, 3),
-        },
+        "roofline": walk_roofline("k_walk", walk_bytes, walk_ms, achieved,
+                                  measured_traffic(args.workload, args.precision, s0["walk_waves"])),
     }
-    if out["roofline"]["traffic"]:
-        hbm = out["roofline"]["traffic"] / (walk_ms * 1e-3) / 1e9
-        out["roofline"]["hbm_measured_gbs"] = round(hbm, 1)
-        out["roofline"]["hbm_measured_frac"] = round(hbm / HBM_PEAK_GBS, 4)
     if not args.no_cpu:
         log(f"cpu baseline (oracle, whole batch, {host_threads()} threads)")
         out["cpu_baseline"] = cpu_baseline_batch(mats, seeds, walks, drop, tol, Bh, off)
@@ -577,22 +565,38 @@ def run_learned(args):
         "phase_ms_uniform": {k: round(v, 2) for k, v in uniform[-1]["stats"]["phase_ms"].items()},
         "train": {"pilot_s": round(t1 - t0, 3),
                   "fit_s": round(t2 - t1, 3), "loss": loss, "target_var": var_y},
-        "roofline": {
-            "kernel": "k_walk",
-            "bound": "hbm",
-            "achieved": round(achieved, 1),
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": None,
-            "alg_bytes_per_launch": walk_bytes,
-            "avg_launch_ms": round(walk_ms, 3),
-        },
+        "roofline": walk_roofline("k_walk", walk_bytes, walk_ms, achieved, None),
     }
     print(json.dumps(out), flush=True)
 
 
-WALK_SOURCES = ("paper_math_0609672_amd/csrc/walk.hpp", "paper_math_0609672_amd/csrc/common.hpp")
+def walk_roofline(kernel, walk_bytes, walk_ms, effective_gbs, traffic):
+    """The walk kernel against the rate of HBM.  With measured traffic (hardware counters,
+    copy-calibrated) of this kernel, `achieved` is that over the kernel's time.  Else it is the
+    method's algorithmic bytes over it, of which the caches serve part and near records save
+    part, so it may pass the peak: no fraction is given then."""
+    achieved = traffic / (walk_ms * 1e-3) / 1e9 if traffic else effective_gbs
+    r = {
+        "kernel": kernel,
+        "bound": "hbm",
+        "achieved": round(achieved, 1),
+        "achieved_is": "measured traffic / kernel time" if traffic
+                       else "effective (algorithmic bytes / kernel time)",
+        "peak": HBM_PEAK_GBS,
+        "unit": "GB/s",
+        "frac": round(achieved / HBM_PEAK_GBS, 4) if achieved <= HBM_PEAK_GBS else None,
+        "traffic": traffic,
+        "alg_bytes_per_launch": walk_bytes,
+        "effective_gbs": round(effective_gbs, 1),
+        "avg_launch_ms": round(walk_ms, 3),
+    }
+    if traffic:
+        r["hbm_measured_gbs"], r["hbm_measured_frac"] = r["achieved"], r["frac"]
+    return r
+
+
+WALK_SOURCES = ("paper_math_0609672_amd/csrc/walk.hpp", "paper_math_0609672_amd/csrc/handover.hpp",
+                "paper_math_0609672_amd/csrc/common.hpp")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_walk_traffic.json")
 
 
@@ -734,6 +738,8 @@ def main():
     E, N = A.nnz, A.n
     C = metrics.factor_size(s0["nnz_y"], N)
     phases = {k: round(sum(r["stats"]["phase_ms"][k] for r in runs) / K, 3) for k in srw.PHASES}
+    # counters were taken on the workload's own walk budget
+    default_walks = not (args.reuse or args.walks or args.adaptive > 0 or asym)
 
     out = {
         "metric": METRIC,
@@ -776,17 +782,9 @@ def main():
         "solve_depth": depth,
         "solve_head_rows": s0.get("head_rows", 0),
         "phase_ms": phases,
-        "roofline": {
-            "kernel": "k_walk_reuse" if args.reuse else "k_walk",
-            "bound": "hbm",
-            "achieved": round(achieved, 1),
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": None,
-            "alg_bytes_per_launch": walk_bytes,
-            "avg_launch_ms": round(walk_ms, 3),
-        },
+        "roofline": walk_roofline(
+            "k_walk_reuse" if args.reuse else "k_walk", walk_bytes, walk_ms, achieved,
+            measured_traffic(args.workload, args.precision, s0["walk_waves"]) if default_walks else None),
     }
     if args.compare_precision:
         other = "fp32" if args.precision == "fp64" else "fp64"
@@ -821,18 +819,6 @@ def main():
         torch.cuda.synchronize()
         log(f"copy calibration: 3 x {args.copy_calibration} MiB read + written by one kernel")
         del src, dst
-    # counters were taken on the workload's own walk budget
-    default_walks = not (args.reuse or args.walks or args.adaptive > 0 or asym)
-    out["roofline"]["traffic"] = (measured_traffic(args.workload, args.precision, s0["walk_waves"])
-                                  if default_walks else None)
-    # `achieved` is effective bandwidth: the method's algorithmic bytes over the kernel
-    # time.  The caches serve part of them; the measured HBM traffic (hardware counters,
-    # copy-calibrated) over the same time is the achieved HBM bandwidth.
-    out["roofline"]["achieved_is"] = "effective (algorithmic bytes / kernel time)"
-    if out["roofline"]["traffic"]:
-        hbm = out["roofline"]["traffic"] / (out["roofline"]["avg_launch_ms"] * 1e-3) / 1e9
-        out["roofline"]["hbm_measured_gbs"] = round(hbm, 1)
-        out["roofline"]["hbm_measured_frac"] = round(hbm / HBM_PEAK_GBS, 4)
     if not args.no_cpu and args.adaptive <= 0:
         log(f"cpu baseline (oracle, whole workload, {host_threads()} threads)")
         out["cpu_baseline"] = cpu_baseline(A, walks, drop, args.seed, tol, b_host, two_games=asym,

@@ -74,8 +74,10 @@ typedef struct {
                                   a budget above 8192 on a row that walks fails the
                                   build with SRW_E_ARG before any walk runs          */
     int32_t factor_precision;  /* SRW_FP64                                          */
-    uint64_t max_steps;        /* per-walk step cap, 0 = 2^22; exceeding it fails
-                                  the build with SRW_E_WALK_LIMIT                    */
+    uint64_t max_steps;        /* per-walk step cap, 0 = 2^22, larger than 2^32 - 256
+                                  counts as that at the default refill period;
+                                  exceeding it fails the build with
+                                  SRW_E_WALK_LIMIT                                   */
     int32_t keep;              /* 0 = keep only the factor; 1 = also keep the
                                   transition table and per-row tallies; 2 = also keep
                                   the per-walk records (for export / inspection)    */
@@ -103,11 +105,16 @@ typedef struct {
                                   open segments (else SRW_E_WALK_LIMIT, see
                                   srw_last_error).  0 (default) = off               */
     int32_t walk_waves;        /* waves per compute unit that the persistent walk
-                                  kernel runs: 4..64, rounded down to a multiple of
-                                  4 and capped at what the kernel's registers allow;
-                                  0 = 8.  Fewer walks in flight than the chip can hold
-                                  see shorter memory latency per step, which bounds
-                                  the longest walks; results do not depend on it     */
+                                  kernel starts walks on: 4..64, rounded down to a
+                                  multiple of 4 and capped at what the kernel's
+                                  registers allow; 0 = 8, or 4 where walks are few
+                                  (less than 2^25) or their records pass 256 MB, with
+                                  4 more that join later where walks are many.
+                                  Waves for long walks run beside them as far as the
+                                  chip holds them.  Fewer walks in flight than the chip
+                                  can hold see shorter memory latency per step, which
+                                  bounds the longest walks; results do not depend on
+                                  it                                                 */
     int32_t one_step_exact;    /* 1 (default): the exact one-step treatment of
                                   Section 5.2 (eqs. newy, newz: the first step goes
                                   to a higher-ranked neighbour, rows without one are
@@ -125,9 +132,10 @@ typedef struct {
                                   diagonal block of Y (computed once by the build,
                                   2 x h(h+1)/2 values) and are solved by two dense
                                   products; the other rows are substituted as before
-                                  (of large matrices in random order the next 131,072
-                                  rows by blocks, with the blocks' sparse inverses;
-                                  not with -1).
+                                  (of large matrices in random order, where the first
+                                  rows past the head are long, the next 131,072 rows
+                                  by blocks, with the blocks' sparse inverses; not
+                                  with -1).
                                   0 (default) = min(n, 4096); -1 = none; 1..16384 =
                                   min(n, that), lowered in steps of 64 rows where a
                                   workgroup's LDS cannot hold one column of the
@@ -220,7 +228,8 @@ typedef struct {
                               simulated walks plus the extracted ones              */
     int32_t reuse;         /* srw_options.reuse of the build                        */
     int32_t two_game;      /* 1 for a factor of srw_build_factor_ldu                */
-    int32_t walk_waves;    /* waves per CU the walk kernel ran (0: no walks)        */
+    int32_t walk_waves;    /* waves per CU the walk kernel started walks on at first
+                              (0: no walks)                                        */
     int64_t head_rows;     /* rows of the solves' dense head (0: none)              */
     int32_t walk_lds;      /* 1 if the walk kernel read its records from a copy in
                               each workgroup's LDS (tables of at most the LDS one
@@ -337,7 +346,7 @@ int srw_apply(const srw_factor* F, const double* r, double* z, void* stream);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and
  * the same result bit for bit, with the triangular solves' work vectors and failure
  * flag in a static scratch array of the library (one per device, 34 MiB + 256 B, held
- * until the process ends) instead of stream-ordered allocations.  It calls no
+ * until the process ends) instead of a block of the library's kept memory.  It calls no
  * allocating routine.  Limit: F's rows <= SRW_NOALLOC_MAX_N, else SRW_E_ARG (see
  * srw_last_error).  Every call on a device shares that device's scratch: calls that
  * overlap on one device (other streams, other threads) race and must be serialised by

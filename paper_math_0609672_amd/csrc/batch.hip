@@ -236,8 +236,8 @@ __global__ __launch_bounds__(BLOCK) void k_tile(Tiles tl, int nrhs, const int64_
     }
 }
 
-// One thread per system: sum the partials of its matrix's tiles in order, then the
-// scalar update of `op`.
+// Sixteen lanes per system: the partials of its matrix's tiles, every sixteenth a lane, the
+// lanes' sums by a butterfly, then the scalar update of `op`.
 __global__ void k_bfinal(int64_t nsys, int nrhs, const int64_t* __restrict__ mat_tile,
                          const double* __restrict__ partials, Sys* __restrict__ sys, int op,
                          double tol, int32_t max_iter, int* __restrict__ active_count)

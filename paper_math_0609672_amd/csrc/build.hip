@@ -1608,7 +1608,7 @@ int build_factor_impl(const srw_csr* A, int32_t walks_per_row, double drop_tol, 
         const int64_t norder = nlong + nslab_rows;
         int32_t max_budget = 0;
         std::memcpy(&max_budget, &pinned[3], sizeof(int32_t));
-        // a chunk descriptor packs the first walk of a chunk into 16 bits and the tally
+        // a chunk descriptor packs the first walk of a chunk into 13 bits and the tally
         // holds a row's ends in LDS: per-row budgets above 8192 are refused here, before
         // any walk runs
         if (max_budget > 8192) {

@@ -10,9 +10,10 @@
 //              w_i = sum over column i of X of c
 // Both are rows of one longer triangular system in (c of a block, z of it, c of the next,
 // ...), which the same sync-free kernel substitutes: m chain rows make 2 m rows.
-// 33 blocks of 131,072 rows, one application without and with the plan, in us: 128^3 2,847
-// and 2,176, 64^3 1,050 and 757, geometric graph of 2M nodes 8,054 and 6,100; the plan adds
-// 2 ms to the 109.6 ms build of 128^3.  Dense inverses of blocks of 2,048 rows instead
+// (Where the first rows past the head are short the solves do without: see the rule of the
+// build.)  33 blocks of 131,072 rows, one application without and with the plan, in us: 128^3
+// 2,847 and 2,176, 64^3 1,050 and 757, geometric graph of 2M nodes 8,054 and 6,100; the plan
+// adds 2 ms to the 109.6 ms build of 128^3.  Dense inverses of blocks of 2,048 rows instead
 // (16.8 MB a block and direction) came to 2,375, 850 and 6,142.
 #include <hip/hip_runtime.h>
 

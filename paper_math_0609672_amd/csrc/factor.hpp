@@ -6,10 +6,6 @@
 #include "common.hpp"
 #include "pool.hpp"
 
-// Library-owned preconditioner.  Node labels are the caller's row indices; Y is
-// stored by rows (CSR, ascending node id per row, strictly lower in rank).  The
-// triangular solves run over a solve plan: the rows of Y and of Y^T listed by slot --
-// the position of a row in the order the solves take -- with columns given as slots.
 // The first rows past the head as a longer triangular system of fewer levels (chain.hip):
 // 2 m rows in the order they are substituted, for either direction.  A row's place (pos) is
 // its slot, or n + its chain row for the c of a block; columns are places.
@@ -23,6 +19,10 @@ struct ChainPlan {
     void *fval = nullptr, *bval = nullptr;
 };
 
+// Library-owned preconditioner.  Node labels are the caller's row indices; Y is
+// stored by rows (CSR, ascending node id per row, strictly lower in rank).  The
+// triangular solves run over a solve plan: the rows of Y and of Y^T listed by slot --
+// the position of a row in the order the solves take -- with columns given as slots.
 struct srw_factor {
     int64_t n = 0;
     int64_t nnz_a = 0;
@@ -132,8 +132,9 @@ constexpr int64_t CHAIN_PLAN_ROWS = 131072;
 // times that of the 128^3 grid's default head (4,096 rows, 0.32M entries, 1.3 ms)
 constexpr int64_t HEAD_COST = (int64_t)8 << 30;
 
-// Device allocations tracked by an owner list (released together).  With a chunk size, requests up to half a chunk are carved out of shared chunks
-// (256-byte aligned), larger ones get a block of their own.
+// Device allocations tracked by an owner list (released together).  With a chunk size,
+// requests up to half a chunk are carved out of shared chunks (256-byte aligned), larger ones
+// get a block of their own.
 struct Arena {
     std::vector<void*> blocks;
     hipError_t last = hipSuccess;

@@ -18,7 +18,7 @@ namespace srw {
 
 namespace {
 
-constexpr int BLOCK = 256;  // (row_times takes 256 rows)
+constexpr int BLOCK = 256;  // (row_times takes at most 256 rows)
 constexpr int RED_GRID = 1024;  // blocks of every reducing kernel (grid-stride)
 
 enum Scalar : int { S_RHO = 0, S_PQ, S_ALPHA, S_RR, S_RHO_NEW, S_BETA, S_BB, S_COUNT };

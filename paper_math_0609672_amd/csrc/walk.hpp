@@ -35,7 +35,8 @@
 // already (the walk kernel makes each block of eight draws one step ahead) and loads
 // the bucket line of that draw: one dependent load per step instead of two.  The line
 // words of entries (and word 3) carry the target's kb in their top bits when the
-// records are bucketed (all main lines below 2^LINE_KB_SHIFT).  The first line and the
+// records are bucketed (all walk lines below 2^LINE_KB_SHIFT; start records follow them, and
+// a walk's start line is used as it is).  The first line and the
 // continuation lines stay: a walk of the plain estimator starts from its row's own
 // record.
 //
@@ -544,7 +545,7 @@ __device__ __forceinline__ void emit_walks(const WalkArgs& a, bool em, uint32_t 
 // (one scalar load of the record, compares and selects on the scalar unit), the lanes
 // make the draws, 64 Philox blocks at a time.  A step then takes 0.2 us on the grid and
 // 0.42 us on the graph (idle chip).  Walk kernel with walks handed over, on the same
-// records: graph 780 -> 480 ms; grid 64^3 70 -> 34 ms; the grid 128^3 is bound by the
+// records: graph 780 -> 414 ms; grid 64^3 70 -> 34 ms; the grid 128^3 is bound by the
 // bulk waves.
 constexpr uint32_t HAND_MIN_AGE = 64;   // steps before a walk may move
 constexpr uint32_t HAND_GROUPS = 8;     // groups of eight steps between a bulk wave's looks
