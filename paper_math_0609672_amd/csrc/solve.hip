@@ -330,6 +330,12 @@ __device__ __forceinline__ V group_reduce(V x, F f)
 // 8,150; 64^3 1,211 and 1,062; 2D grid of 490,000 674 and 626.
 constexpr int ROW_U = 2;
 
+// A row's products and their sum are in 64 bits, whatever the factor's type, and rounded once.
+// The plan rounds to FP32 once more a row (c) and its X; with sums in FP32 its solutions were
+// further off than a substitution's (3D grid of 140,556 rows with few grounded nodes, twelve
+// solves, mean error against 64 bits: substitution 1.29e-7, plan 1.95e-7, this way 0.98e-7;
+// 56^3 1.02e-7, 1.13e-7, 0.71e-7; 2D grid 500^2, which takes no plan, 0.84e-7, 0.85e-7,
+// 0.55e-7), in the same time (graph of 2M nodes, PCG with an FP32 factor, 76.0 and 76.3 ms).
 // PLAN: rows 0..hi-1 of the chain plan, taken in their order; pos is a row's place, below n
 // for a row of X (no right-hand side), n + (chain row) for a c, h the first chain slot.
 template <typename T, bool FWD, int LPR, bool PLAN>
@@ -358,17 +364,20 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t 
     const int64_t step = nw * G;
     auto slot = [&](int64_t i) { return FWD || PLAN ? lo + i : hi - 1 - i; };
     // what the row at place p (of node v) is made of, but for other rows' values
-    auto w_of = [&](int64_t p, int32_t v) -> T {
-        if (PLAN && p < n) return T(0);
-        return FWD ? w[PLAN ? p - n + h : p] : (T)rhs[v];
+    auto w_of = [&](int64_t p, int32_t v) -> double {
+        if (PLAN && p < n) return 0.0;
+        return FWD ? (double)w[PLAN ? p - n + h : p] : rhs[v];
     };
-    auto d_of = [&](int64_t p) -> T { return FWD && !(PLAN && p < n) ? dslot[PLAN ? p - n + h : p] : T(1); };
+    auto d_of = [&](int64_t p) -> double {
+        return FWD && !(PLAN && p < n) ? (double)dslot[PLAN ? p - n + h : p] : 1.0;
+    };
     // row i (this one), i + step (b: bounds and node known) and i + 2 step (a)
     int64_t i = wid * G + grp;
     int64_t q0 = 0, q1 = 0, bq0 = 0, bq1 = 0;
     int32_t node = 0, bnode = 0, at = 0, bat = 0;
     int32_t c[ROW_U];
-    T v[ROW_U], base = T(0);
+    T v[ROW_U];
+    double base = 0.0;
     if (i < m) {
         q0 = ptr[slot(i)];
         q1 = ptr[slot(i) + 1];
@@ -407,7 +416,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t 
             nc[k] = q < bq1 ? col[q] : 0;
             nv[k] = q < bq1 ? val[q] : T(0);
         }
-        T nw_ = T(0), nd = T(1);
+        double nw_ = 0.0, nd = 1.0;
         if (i + step < m) {
             nw_ = w_of(bat, bnode);
             nd = d_of(bat);
@@ -420,7 +429,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t 
         }
         bool done = i >= m;
         int64_t qn = q0 + ROW_U * LPR;  // the row's entries past those in registers
-        T acc = T(0);
+        double acc = 0.0;
         uint32_t spins = 0;
         int64_t t0 = 0;
         for (;;) {
@@ -438,7 +447,7 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t 
             const bool ready = !done && !gmiss;
             if (ready) {
 #pragma unroll
-                for (int k = 0; k < ROW_U; ++k) acc += v[k] * __builtin_bit_cast(T, bits[k]);
+                for (int k = 0; k < ROW_U; ++k) acc += (double)v[k] * (double)__builtin_bit_cast(T, bits[k]);
                 if (qn < q1) {  // a long row: its next entries
 #pragma unroll
                     for (int k = 0; k < ROW_U; ++k) {
@@ -457,10 +466,10 @@ __global__ __launch_bounds__(BLOCK) void k_trsv(int64_t lo, int64_t hi, int64_t 
             }
             const bool fin = ready && qn >= q1 + ROW_U * LPR;
             if (ballot(fin) != 0) {
-                const T sum = group_reduce<LPR>(acc, [](T x, T y) { return x + y; });
+                const double sum = group_reduce<LPR>(acc, [](double x, double y) { return x + y; });
                 if (fin) {
                     if (gl == 0) {
-                        const T x = base - sum;
+                        const T x = (T)(base - sum);
                         __hip_atomic_store((U*)sol + at, __builtin_bit_cast(U, x), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                         if (out && (!PLAN || at < n)) out[node] = (double)x;
